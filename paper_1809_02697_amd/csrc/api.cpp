@@ -202,12 +202,12 @@ int stream_workspace(hipStream_t st, size_t bytes, float** ws) {
 
 // Optional override of the launch configuration, "fk,fp,split[,waves]", for
 // tuning sweeps of the standalone call.
-bool env_config(ConvConfig* c) {
+bool env_config(const ConvShape& s, ConvConfig* c) {
     const char* v = std::getenv("NEO_CONV_CONFIG");
     if (!v || !*v) return false;
     ConvConfig t{1, 1, 1, 4};
     const int n = std::sscanf(v, "%d,%d,%d,%d", &t.fk, &t.fp, &t.split, &t.waves);
-    if (n < 3 || !conv_config_valid(t)) return false;
+    if (n < 3 || !(conv_config_valid(t) || conv_h2_config_valid(s, t))) return false;
     *c = t;
     return true;
 }
@@ -289,7 +289,7 @@ int conv_prepare(const char* fn, const float* x, int x_block, int N, int C, int 
         return fail(NEO_ERR_UNSUPPORTED, f + ": input or filter of 2 GiB or more");
     ConvConfig cfg = choose_conv_config(s);
     (void)tuned_config(s, false, &cfg);
-    env_config(&cfg);
+    env_config(s, &cfg);
     const int T = cdiv(C, 16) * R * S;
     if (cfg.split > T) cfg.split = T;
     *shape = s;

@@ -1,7 +1,7 @@
 // Blocked convolution on fp32 MFMA (gfx950): launch configuration, cost model
 // and launcher.  The kernels are in conv_kernel.h; this file instantiates the
 // NCHW16c -> NCHW16c family, conv_xy.hip every other pair of blocks.
-#include "conv_kernel.h"
+#include "conv_h2.h"
 
 namespace neo {
 
@@ -11,6 +11,10 @@ static_assert(kMaxGroup == kMaxGroupConvs, "group size");
 
 extern template hipError_t conv_detail::dispatch_all<true>(const ConvConfig&, int, bool, bool,
                                                            const ConvArgs&, hipStream_t);
+extern template hipError_t conv_detail::dispatch_h2<false, false>(const ConvConfig&, int, const H2Args&, hipStream_t);
+extern template hipError_t conv_detail::dispatch_h2<false, true>(const ConvConfig&, int, const H2Args&, hipStream_t);
+extern template hipError_t conv_detail::dispatch_h2<true, false>(const ConvConfig&, int, const H2Args&, hipStream_t);
+extern template hipError_t conv_detail::dispatch_h2<true, true>(const ConvConfig&, int, const H2Args&, hipStream_t);
 
 int conv_group(const ConvShape& s, const ConvConfig& c) {
     if (conv_small_c(s)) return 1;
@@ -25,6 +29,86 @@ int conv_steps(const ConvShape& s, const ConvConfig& c) {
     return cdiv(s.C, 16) / conv_group(s, c) * s.R * s.S;
 }
 
+namespace {
+
+// How the two-term kernel cuts the output pixels into tiles of P and the input
+// patch of one: the patch pixels (at most), and the tiles.
+struct H2Geometry {
+    int kind, ltw, th, PW, patch;
+    long tiles;
+};
+
+constexpr int kH2MaxPatch = 512;
+
+// Whole rows of consecutive pixels (which may run over several images), or
+// blocks of th x tw pixels of one image, whichever costs least: per channel
+// block and tile the matrix instructions take 3 P cycles per kernel entry
+// and a patch pixel's load, conversion and store about 1.5.  False if no patch
+// fits.
+bool h2_geometry(const ConvShape& s, int P, H2Geometry* out) {
+    const long M = (long)s.N * s.OH * s.OW;
+    if (s.R == 1 && s.S == 1) {
+        *out = H2Geometry{kH2Point, 0, 0, 1, P, (M + P - 1) / P};
+        return true;
+    }
+    double best = 1e300;
+    auto consider = [&](int kind, int ltw, int th, long PW, long rows, long tiles) {
+        if (PW * rows > kH2MaxPatch) return;
+        const double cost = (double)tiles * (3.0 * P * s.R * s.S + 1.5 * (double)(PW * rows));
+        if (cost < best) {
+            best = cost;
+            *out = H2Geometry{kind, ltw, th, (int)PW, (int)(PW * rows), tiles};
+        }
+    };
+    {
+        // output rows that P consecutive pixels touch, and images those rows lie in
+        const long nr = std::min<long>((P - 2) / s.OW + 2, (long)s.N * s.OH);
+        const long ni = std::min<long>(nr < 2 ? 1 : (nr - 2) / s.OH + 2, s.N);
+        consider(kH2Rows, 0, 0, (long)(s.OW - 1) * s.sw + s.S, nr * s.sh + ni * std::max(s.R - s.sh, 0), (M + P - 1) / P);
+    }
+    for (int ltw = 2; (1 << ltw) <= P; ++ltw) {
+        const int tw = 1 << ltw, th = P / tw;
+        consider(kH2Block, ltw, th, (long)(tw - 1) * s.sw + s.S, (long)(th - 1) * s.sh + s.R,
+                 (long)s.N * cdiv(s.OH, th) * cdiv(s.OW, tw));
+    }
+    return best < 1e300;
+}
+
+// Patch pixels / 64 that the kernel is instantiated for.
+int h2_patch_blocks(const H2Geometry& g) {
+    const int n = cdiv(g.patch, 64);
+    return g.kind == kH2Point ? n : n <= 2 ? 2 : n <= 3 ? 3 : n <= 5 ? 5 : 8;
+}
+
+int h2_pixels(const ConvConfig& c) { return 32 * c.fp * (kH2Waves / c.fk); }
+
+}  // namespace
+
+bool conv_h2_config_valid(const ConvShape& s, const ConvConfig& c) {
+    // (the folded global pool needs the tile kernel's epilogue)
+    if (!conv_h2(c) || !(c.fk == 2 || c.fk == 4) || !(c.fp == 2 || c.fp == 4) || c.split < 1 || c.split > 64 ||
+        s.gap || conv_small_c(s))
+        return false;
+    H2Geometry g;
+    return h2_geometry(s, h2_pixels(c), &g) && g.tiles * cdiv(cdiv(s.K, s.yb) * s.yb, 32 * c.fk) * c.split < (1L << 30) &&
+           h2_filter_floats(s) * 4 < (1L << 31);
+}
+
+int conv_h2_chunks(const ConvShape& s, const ConvConfig& c) {
+    const int CB = cdiv(s.C, 16);
+    return s.R == 1 && s.S == 1 ? cdiv(CB, h2_blocks(h2_pixels(c) / 64)) : CB;
+}
+
+long h2_filter_floats(const ConvShape& s) {
+    const long kb = cdiv(cdiv(s.K, 16), 2);
+    return kb * cdiv(s.C, 16) * s.R * s.S * 512 + kb * 32;
+}
+
+hipError_t launch_h2_filter(const ConvShape& s, const float* w, float* out, hipStream_t st) {
+    const int KB = cdiv(s.K, 16), steps = cdiv(s.C, 16) * s.R * s.S;
+    return launch_h2_split(w, KB, steps, out, reinterpret_cast<int*>(out + (long)cdiv(KB, 2) * steps * 512), st);
+}
+
 bool conv_config_valid(const ConvConfig& c) {
     const bool tile = (c.fk == 1 || c.fk == 2 || c.fk == 4) && (c.fp == 1 || c.fp == 2 || c.fp == 4);
     const bool waves = c.waves == 1 || c.waves == 2 || c.waves == 4 ||
@@ -37,7 +121,7 @@ bool conv_config_valid(const ConvConfig& c) {
 // (each step: its MFMAs, or the measured ~300-cycle bookkeeping-and-load
 // chain when a SIMD has a single wave, shared between resident waves), plus
 // the extra kernel and partial round trip of a split.
-ConvConfig choose_conv_config(const ConvShape& s) {
+ConvConfig choose_tile_config(const ConvShape& s, double* us) {
     const int KB = cdiv(s.K, 16), MP = cdiv(s.N * s.OH * s.OW, 16);
     const double kClk = 2400.0;  // cycles per microsecond
     ConvConfig best{1, 1, 1, 4};
@@ -73,6 +157,64 @@ ConvConfig choose_conv_config(const ConvShape& s) {
             }
         }
     }
+    if (us) *us = best_t;
+    return best;
+}
+
+namespace {
+
+// Time of the two-term kernel in microseconds.  A workgroup alone on its CU
+// walks a chain: per step 133 + 185 fp cycles, per chunk 337 for each float4 of
+// a thread's patch, and 10,400 to set up, sample and store; several on one CU
+// share its matrix and vector units, where a step takes 96 fp + 181 cycles and
+// a float4 264.  The constants are a fit to 2,174 measured launches (220
+// shapes of 1x1 to 7x7 kernels at batch 1 to 32, every tile, splits 1 to 8):
+// mean deviation 11 %.
+double h2_time_us(const ConvShape& s, const ConvConfig& c) {
+    H2Geometry g;
+    if (!conv_h2_config_valid(s, c) || !h2_geometry(s, h2_pixels(c), &g)) return 1e30;
+    const int CB = cdiv(s.C, 16), ni = h2_patch_blocks(g), uc = g.kind == kH2Point ? h2_blocks(ni) : 1;
+    const int chunks = cdiv(conv_h2_chunks(s, c), c.split);
+    const double steps = (double)std::min(uc, CB) * s.R * s.S, items = uc * ni;
+    const long lds = 2L * uc * 4 * (64 * ni + 4) * 16 + 2048;
+    const double occ = (double)std::max<long>(1, std::min<long>(c.fp == 4 ? 2 : 3, 163840 / lds));
+    const double chain = chunks * (steps * (133.0 + 185.0 * c.fp) + 337.0 * items) + 10400.0;
+    const double share = chunks * (steps * (181.0 + 96.0 * c.fp) + 264.0 * items) + 5600.0;
+    const double per_cu = (double)g.tiles * cdiv(s.K, 32 * c.fk) * c.split / 256.0;
+    const double full = std::floor(per_cu / occ), rest = std::ceil(per_cu - full * occ - 1e-9);
+    double t = full * std::max(chain, occ * share);
+    if (rest > 0) t += std::max(chain, rest * share);
+    double us = 2.2 + t / 2400.0;
+    if (c.split > 1) us += 1.3 + 2.0 * conv_workspace_bytes(s, c) / 3.8e6;
+    return us;
+}
+
+// The tile kernel's model is too fast by 1.2 to 2.3 (the middle half of those
+// shapes: 1.3 to 1.8), the two-term kernel's is not, so the line between them
+// lies at 1.4 times the tile model's time: of the 220 shapes 55 then take the
+// two-term kernel, 1.57 times as fast on average, one of them 7 % slower.
+constexpr double kH2Line = 1.4;
+
+}  // namespace
+
+ConvConfig choose_conv_config(const ConvShape& s) {
+    double tile_us = 0;
+    ConvConfig best = choose_tile_config(s, &tile_us);
+    double best_us = kH2Line * tile_us;
+    // never more partials than the tile kernel's choice asks for: a call that
+    // needed no workspace (under stream capture, say) still needs none
+    const size_t ws = conv_workspace_bytes(s, best);
+    for (int fk : {2, 4})
+        for (int fp : {2, 4})
+            for (int sp : {1, 2, 4, 8}) {
+                const ConvConfig c{fk, fp, sp, 0};
+                if (sp > 1 && (conv_workspace_bytes(s, c) > ws || sp > conv_h2_chunks(s, c))) continue;
+                const double us = h2_time_us(s, c);
+                if (us < best_us) {
+                    best_us = us;
+                    best = c;
+                }
+            }
     return best;
 }
 
@@ -89,6 +231,8 @@ constexpr long kKFirstMinWgs = 1024;  // launches this large take channel tiles 
 // channel groups per reduction step.
 ConvArgs make_args(const ConvShape& s, const ConvConfig& c, int G, const float* x, const float* w,
                    bool wmfma, const float* bias, const float* res, float* y, float* ws) {
+    // a workgroup's tile in blocks of 16 (the two-term kernel: 32 fk channels)
+    const int bk = conv_h2(c) ? 2 * c.fk : c.fk, bp = c.fp;
     ConvArgs a;
     a.x = x;
     a.w = w;
@@ -133,14 +277,14 @@ ConvArgs make_args(const ConvShape& s, const ConvConfig& c, int G, const float* 
     a.w_bytes = (int)((wmfma ? kernel_filter_floats(s) : (long)a.KB * a.CB * a.RS * 256) * 4);
     a.div_ohw = make_fastdiv((unsigned)(s.OH * s.OW));
     a.div_ow = make_fastdiv((unsigned)s.OW);
-    a.div_npx = make_fastdiv((unsigned)cdiv(a.M, 16 * c.fp));
-    a.div_nkb = make_fastdiv((unsigned)cdiv(a.KBk, c.fk));
+    a.div_npx = make_fastdiv((unsigned)cdiv(a.M, 16 * bp));
+    a.div_nkb = make_fastdiv((unsigned)cdiv(a.KBk, bk));
     // Large launches take channel tiles first: the workgroups that read one
     // input tile then run on one XCD and share its L2.  Measured on MI355X
     // (tuned, fused plans): from 1024 workgroups up, ResNet-50 batch 32 runs
     // 2.76 ms against 2.82 ms with pixel tiles first, batch 1 and VGG-16
     // batch 1 unchanged; from 512 up, batch 1 is 1.3 % slower.
-    a.kfirst = (long)cdiv(a.M, 16 * c.fp) * cdiv(a.KBk, c.fk) >= kKFirstMinWgs;
+    a.kfirst = (long)cdiv(a.M, 16 * bp) * cdiv(a.KBk, bk) >= kKFirstMinWgs;
     a.gap = s.gap;
     return a;
 }
@@ -149,10 +293,45 @@ ConvArgs make_args(const ConvShape& s, const ConvConfig& c, int G, const float* 
 
 hipError_t launch_conv2d(const ConvShape& s, const ConvConfig& c, const float* x, const float* w,
                          bool wmfma, const float* bias, const float* res, float* y, float* ws,
-                         hipStream_t st) {
+                         hipStream_t st, const float* wh2) {
     if (c.fp == 0) {  // the streaming pointwise kernel (filter in kernel order)
         if (!wmfma || !conv_stream_config_valid(s, c)) return hipErrorInvalidValue;
         return launch_conv_stream(s, c, x, w, bias, res, y, st);
+    }
+    if (conv_h2(c)) {
+        H2Geometry g;
+        if (!conv_h2_config_valid(s, c) || !conv_blocks_valid(s) || (wmfma && !wh2) ||
+            !h2_geometry(s, h2_pixels(c), &g))
+            return hipErrorInvalidValue;
+        H2Args h;
+        h.a = make_args(s, c, 1, x, wmfma ? wh2 : w, wmfma, bias, res, y, ws);
+        ConvArgs& a = h.a;
+        h.chunks = conv_h2_chunks(s, c);
+        a.split = (c.split > 1 && ws) ? std::min(c.split, h.chunks) : 1;
+        a.div_npx = make_fastdiv((unsigned)g.tiles);
+        a.kfirst = g.tiles * a.div_nkb.d >= kKFirstMinWgs;
+        h.w32 = w;
+        h.w32_bytes = a.w_bytes;
+        h.wexp = nullptr;
+        if (wmfma) {
+            const long kb = cdiv(a.KB, 2);
+            a.w_bytes = (int)(kb * a.CB * a.RS * 2048);
+            h.wexp = reinterpret_cast<const int*>(wh2 + kb * a.CB * a.RS * 512);
+        }
+        h.kind = g.kind;
+        h.ltw = g.ltw;
+        h.th = g.th;
+        h.PW = g.PW;
+        h.SF = (s.OH - 1) * s.sh + s.R;
+        h.div_pw = make_fastdiv((unsigned)g.PW);
+        h.div_sf = make_fastdiv((unsigned)h.SF);
+        const int tx = g.kind == kH2Block ? cdiv(s.OW, 1 << g.ltw) : 1;
+        h.div_tx = make_fastdiv((unsigned)tx);
+        h.div_tpi = make_fastdiv((unsigned)(g.kind == kH2Block ? tx * cdiv(s.OH, g.th) : 1));
+        const int n = h2_patch_blocks(g);
+        const bool xy = s.xb != 16 || s.yb != 16;
+        if (wmfma) return xy ? dispatch_h2<true, true>(c, n, h, st) : dispatch_h2<true, false>(c, n, h, st);
+        return xy ? dispatch_h2<false, true>(c, n, h, st) : dispatch_h2<false, false>(c, n, h, st);
     }
     if (!conv_config_valid(c) || !conv_blocks_valid(s)) return hipErrorInvalidValue;
     if (s.gap && s.N != 1) return hipErrorInvalidValue;
@@ -197,7 +376,7 @@ ConvConfig choose_group_config(const ConvShape* s, int n) {
             big = i;
         }
     }
-    ConvConfig c = choose_conv_config(s[big]);
+    ConvConfig c = choose_tile_config(s[big], nullptr);
     c.split = 1;
     for (int fk : {c.fk, 2, 1})
         for (int fp : {c.fp, 2, 1})

@@ -50,6 +50,16 @@ struct ConvConfig {
     int fk, fp, split, waves;
 };
 bool conv_config_valid(const ConvConfig& c);
+// Two-term fp16 convolution (conv_h2.h): waves = 0 names the kernel whose
+// workgroup of four waves computes 32 fk channels x 32 fp (4 / fk) pixels, its
+// reduction split over `split` workgroups.  Plans (filters in kernel order)
+// hand it the filter's converted terms too: h2_filter_floats floats, written
+// by launch_h2_filter.
+inline bool conv_h2(const ConvConfig& c) { return c.fp != 0 && c.waves == 0; }
+bool conv_h2_config_valid(const ConvShape& s, const ConvConfig& c);
+int conv_h2_chunks(const ConvShape& s, const ConvConfig& c);  // the most that split can be
+long h2_filter_floats(const ConvShape& s);
+hipError_t launch_h2_filter(const ConvShape& s, const float* w, float* out, hipStream_t st);
 // Inputs with at most 4 channels (network stems) take the small-channel path:
 // a reduction step is (filter row r, group u of 4 filter columns) instead of
 // (channel block, kernel entry).
@@ -67,6 +77,9 @@ inline bool conv_blocks_valid(const ConvShape& s) {
 // small-channel path), and the reduction steps of one output tile.
 int conv_group(const ConvShape& s, const ConvConfig& c);
 int conv_steps(const ConvShape& s, const ConvConfig& c);
+// The cost models' choice: among the tile kernel's configurations (us: its
+// modelled time, may be null), and among both kernels'.
+ConvConfig choose_tile_config(const ConvShape& s, double* us);
 ConvConfig choose_conv_config(const ConvShape& s);
 // Workspace of a split reduction (partial sums of every split), in bytes.
 size_t conv_workspace_bytes(const ConvShape& s, const ConvConfig& c);
@@ -96,7 +109,8 @@ hipError_t launch_conv_stream(const ConvShape& s, const ConvConfig& c, const flo
 inline bool conv_any_config_valid(const ConvConfig& c) {
     const bool stream = c.fp == 0 && c.split == 1 && (c.fk == 1 || c.fk == 2 || c.fk == 4) &&
                         (c.waves == 1 || c.waves == 2 || c.waves == 4 || c.waves == 8);
-    return stream || conv_config_valid(c);
+    const bool h2 = conv_h2(c) && (c.fk == 2 || c.fk == 4) && (c.fp == 2 || c.fp == 4) && c.split >= 1 && c.split <= 64;
+    return stream || h2 || conv_config_valid(c);
 }
 
 // Winograd F(2x2, 3x3) convolution (winograd.hip): 3x3, stride 1, NCHW16c in
@@ -159,10 +173,11 @@ hipError_t launch_conv_int8(const ConvShape& s, const ConvConfig& c, const int8_
 // or null; res: NCHW[yb]c [N][ceil(K/yb)][OH][OW][yb] or null; y: NCHW[yb]c
 // view (padding lanes of the last block written as 0).  ws: workspace of at
 // least conv_workspace_bytes (a split is only used when it is given).  x and w
-// must each be below 2 GiB.
+// must each be below 2 GiB.  wh2: with wmfma and a two-term configuration, the
+// converted filter.
 hipError_t launch_conv2d(const ConvShape& s, const ConvConfig& c, const float* x, const float* w,
                          bool wmfma, const float* bias, const float* res, float* y, float* ws,
-                         hipStream_t st);
+                         hipStream_t st, const float* wh2 = nullptr);
 
 // Pooling on NCHW[xb]c (xb in 4..64); y_off / y_tot: output view in blocks.
 struct PoolShape {

@@ -85,6 +85,8 @@ struct Step {
     long u_off = -1;
     bool wino = false;
     ConvConfig wc{1, 1, 1, 1};
+    // ST_CONV run by the two-term kernel: its converted filter (float offset in d_h2)
+    long h2_off = -1;
     // ST_CONV with NEO_PLAN_INT8: the folded KCRS filter (float offset), the
     // per-channel scales the device packing writes (float offset), the packed
     // int8 filter (byte offset in the int8 arena), the configuration; the
@@ -188,6 +190,7 @@ struct neo_plan {
     // split-reduction workspace shared by the conv steps (they run in order)
     size_t ws_bytes = 0;
     float* d_ws = nullptr;
+    float* d_h2 = nullptr;  // converted filters of the convs the two-term kernel runs
     int out_val = -1;
     int out_dims[4] = {0, 0, 0, 0};
     int input_val = -1;
@@ -832,7 +835,10 @@ void group_ready_convs(neo_plan* P) {
             if (ok) ready.push_back(j);
         }
         for (int j : ready) {
-            if (S[j].kind == ST_CONV && (S[j].i8 || conv_group_eligible(S[j].cs)))
+            // (without the local search, which compares both, a conv that fills
+            // the chip by itself keeps the two-term kernel)
+            const bool alone = !(P->flags & NEO_PLAN_TUNE) && conv_h2(S[j].cc);
+            if (S[j].kind == ST_CONV && (S[j].i8 || (conv_group_eligible(S[j].cs) && !alone)))
                 convs.push_back(j);
             else if (pools_ride && (S[j].kind == ST_MAXPOOL || S[j].kind == ST_AVGPOOL) && S[j].p8 < 0)
                 pools.push_back(j);
@@ -936,9 +942,9 @@ void fuse_gap(neo_plan* P) {
         for (size_t v = 0; v < P->vals.size(); ++v) ok = ok && !(P->vals[v].view && is_pooled((int)v));
         if (!ok || dense.empty()) continue;
         S[pi].cs.gap = 1;
-        // the streaming pointwise kernel has no folded pool: the tile kernel's
-        // configuration for this shape instead
-        if (S[pi].cc.fp == 0) S[pi].cc = choose_conv_config(S[pi].cs);
+        // the streaming and the two-term kernel have no folded pool: the tile
+        // kernel's configuration for this shape instead
+        if (S[pi].cc.fp == 0 || conv_h2(S[pi].cc)) S[pi].cc = choose_tile_config(S[pi].cs, nullptr);
         const int hw = iv.H * iv.W;
         for (size_t k : dense) {
             S[k].in = in;  // reads the conv's sums (and so runs after it)
@@ -1653,6 +1659,24 @@ int search_schemes(neo_plan* P) {
 
 }  // namespace
 
+// The converted filters of the convs that the two-term kernel runs, once their
+// configurations are settled.
+static hipError_t convert_h2_filters(neo_plan* P) {
+    long floats = 0;
+    for (Step& st : P->steps)
+        if (st.kind == ST_CONV && !st.i8 && !st.wino && conv_h2(st.cc)) {
+            st.h2_off = floats;
+            floats += (h2_filter_floats(st.cs) + 63) / 64 * 64;
+        }
+    if (!floats) return hipSuccess;
+    hipError_t e = hipMalloc(&P->d_h2, (size_t)floats * 4);
+    for (const Step& st : P->steps)
+        if (st.h2_off >= 0 && e == hipSuccess)
+            e = launch_h2_filter(st.cs, P->d_params + st.w_off, P->d_h2 + st.h2_off, nullptr);
+    if (e == hipSuccess) e = hipDeviceSynchronize();
+    return e;
+}
+
 extern "C" {
 
 int neo_layout_search(const neo_node* nodes, int n_nodes, int N, int C, int H, int W, int block,
@@ -1843,7 +1867,10 @@ int neo_plan_create(const neo_node* nodes, int n_nodes, int N, int C, int H, int
             if (st.kind == ST_CONV)
                 P->ws_bytes = std::max(P->ws_bytes, conv_workspace_bytes(st.cs, st.wino ? st.wc : st.cc));
         if (P->ws_bytes) e = hipMalloc(&P->d_ws, P->ws_bytes);
+        if (e == hipSuccess) e = convert_h2_filters(P);
         if (e != hipSuccess) {
+            if (P->d_ws) (void)hipFree(P->d_ws);
+            if (P->d_h2) (void)hipFree(P->d_h2);
             (void)hipFree(P->d_params);
             (void)hipFree(P->d_act);
             if (P->cap_stream) (void)hipStreamDestroy(P->cap_stream);
@@ -1983,7 +2010,8 @@ static int enqueue_step(neo_plan* P, const Step& s, const float* x_nchw, float* 
                 e = launch_conv2d(s.cs, s.cc, val_ptr(P, s.in, x_nchw, y_out), prm + s.w_off, true,
                                   s.b_off >= 0 ? prm + s.b_off : nullptr,
                                   s.res >= 0 ? val_ptr(P, s.res, x_nchw, y_out) : nullptr,
-                                  val_ptr(P, s.out, x_nchw, y_out), P->d_ws, st);
+                                  val_ptr(P, s.out, x_nchw, y_out), P->d_ws, st,
+                                  s.h2_off >= 0 ? P->d_h2 + s.h2_off : nullptr);
                 break;
             case ST_CONV_GROUP: {
                 const int n = (int)s.members.size();
@@ -2410,7 +2438,7 @@ static int tune_plan(neo_plan* P) {
                            s.b_off >= 0 ? prm + s.b_off : nullptr,
                            s.res >= 0 ? val_ptr(P, s.res, xin, yout) : nullptr,
                            val_ptr(P, s.out, xin, yout), P->cap_stream, &s.cc, &direct_us);
-            if (s.cs.gap && s.cc.fp == 0) s.cc = choose_conv_config(s.cs);
+            if (s.cs.gap && (s.cc.fp == 0 || conv_h2(s.cc))) s.cc = choose_tile_config(s.cs, nullptr);
             if (rc == NEO_OK && s.u_off >= 0 && wino_eligible(s.cs)) {
                 // the Winograd kernel runs the step only where it measures faster
                 float wino_us = 0.f;
@@ -2636,6 +2664,7 @@ void neo_plan_destroy(neo_plan* plan) {
         (void)hipFree(plan->d_params);
         (void)hipFree(plan->d_act);
         if (plan->d_ws) (void)hipFree(plan->d_ws);
+        if (plan->d_h2) (void)hipFree(plan->d_h2);
         if (plan->d_i8) (void)hipFree(plan->d_i8);
         if (plan->d_absmax) (void)hipFree(plan->d_absmax);
     }

@@ -79,6 +79,14 @@ std::vector<ConvConfig> candidates(const ConvShape& s) {
                     if (sp > 1 && conv_workspace_bytes(s, c) > (64u << 20)) continue;
                     out.push_back(c);
                 }
+    for (int fk : {2, 4})
+        for (int fp : {2, 4})
+            for (int sp : {1, 2, 4, 8}) {
+                const ConvConfig c{fk, fp, sp, 0};
+                if (!conv_h2_config_valid(s, c) || conv_h2_chunks(s, c) < sp) continue;
+                if (sp > 1 && conv_workspace_bytes(s, c) > (64u << 20)) continue;
+                out.push_back(c);
+            }
     return out;
 }
 
@@ -102,6 +110,7 @@ bool tuned_config(const ConvShape& s, bool wmfma, ConvConfig* out) {
     if (it == g_db.end()) return false;
     // a stored streaming configuration the shape cannot take is ignored
     if (it->second.cfg.fp == 0 && !conv_stream_config_valid(s, it->second.cfg)) return false;
+    if (conv_h2(it->second.cfg) && !conv_h2_config_valid(s, it->second.cfg)) return false;
     *out = it->second.cfg;
     return true;
 }
@@ -146,7 +155,7 @@ int tune_conv(const ConvShape& s, bool wmfma, const float* x, const float* w, co
     {
         std::lock_guard<std::mutex> lk(g_mu);
         auto it = g_db.find(key_of(s, wmfma, arch));
-        if (it != g_db.end()) {
+        if (it != g_db.end() && (!conv_h2(it->second.cfg) || conv_h2_config_valid(s, it->second.cfg))) {
             *best_out = it->second.cfg;
             if (us_out) *us_out = it->second.us;
             return NEO_OK;
@@ -157,17 +166,24 @@ int tune_conv(const ConvShape& s, bool wmfma, const float* x, const float* w, co
         for (const ConvConfig& c : stream_candidates(s)) cands.push_back(c);
     size_t ws_bytes = 0;
     for (const ConvConfig& c : cands) ws_bytes = std::max(ws_bytes, conv_workspace_bytes(s, c));
-    float* ws = nullptr;
+    float *ws = nullptr, *wh2 = nullptr;
     hipError_t e = hipSuccess;
     if (ws_bytes) e = hipMalloc(&ws, ws_bytes);
-    if (e != hipSuccess) return fail(NEO_ERR_OOM, "tuning workspace allocation");
+    const bool h2 = wmfma && std::any_of(cands.begin(), cands.end(), [](const ConvConfig& c) { return conv_h2(c); });
+    if (h2 && e == hipSuccess) e = hipMalloc(&wh2, (size_t)h2_filter_floats(s) * 4);
+    if (e != hipSuccess) {
+        if (ws) (void)hipFree(ws);
+        return fail(NEO_ERR_OOM, "tuning workspace allocation");
+    }
+    if (h2) e = launch_h2_filter(s, w, wh2, st);
     ConvConfig best = choose_conv_config(s);
     float best_us = 1e30f;
     {
         Events ev;
         for (const ConvConfig& c : cands) {
             float us = 0.f;
-            e = time_launch([&] { return launch_conv2d(s, c, x, w, wmfma, bias, res, y, ws, st); }, st,
+            if (e != hipSuccess) break;
+            e = time_launch([&] { return launch_conv2d(s, c, x, w, wmfma, bias, res, y, ws, st, wh2); }, st,
                             ev.e0, ev.e1, &us);
             if (e != hipSuccess) break;
             if (us < best_us) {
@@ -178,6 +194,7 @@ int tune_conv(const ConvShape& s, bool wmfma, const float* x, const float* w, co
         (void)hipStreamSynchronize(st);
     }
     if (ws) (void)hipFree(ws);
+    if (wh2) (void)hipFree(wh2);
     if (e != hipSuccess) return hip_fail(e, "tuning");
     {
         std::lock_guard<std::mutex> lk(g_mu);
