@@ -4,9 +4,14 @@
 // Same 16x16x4 MFMA tiling as the convolution: A = 16 rows of W (output
 // features), B = 16 rows of x (batch), D[4g+v][i] = y[batch i][feature 4g+v].
 // Both operands are row-major along the reduction axis, so each lane loads one
-// float4 per operand per 16-wide reduction chunk.  The chunks are split over
-// the 4 waves of a workgroup and summed through LDS in a fixed order; U chunks
-// of loads are issued before their MFMAs to keep enough bytes in flight.
+// float4 per operand per 16-wide reduction chunk.  The weight stream bounds
+// it: every load instruction touches 16 rows, 64 bytes of each, so a wave takes
+// two neighbouring chunks (the 128 bytes of a cache line) at a time, with two
+// pairs in flight: more waves or more loads in flight only evict half-read
+// lines from the 32 KB L1 (16 x 25,088 -> 4096: 128 us with single chunks, 113
+// with pairs over 16 waves, 99 over 8; the weights alone take 81 us at the rate
+// of a large copy).  The waves of a workgroup split the chunks and are summed
+// through LDS in wave order.
 //
 // Up to 4 batch rows the layer is a matrix-vector product, a pure weight
 // stream (HBM bound), and a 16-wide MFMA tile would waste 15/16 of its batch
@@ -38,9 +43,6 @@ __device__ inline v4f rows_mean4(const DenseArgs& a, const v4f* x4, int k) {
     return s * a.scale;
 }
 
-constexpr int kWaves = 4;
-constexpr int kU = 4;
-
 // Load 4 consecutive reduction elements starting at k of a row; VEC = row
 // starts are 16-byte aligned (IN % 4 == 0), so a chunk is all in or all out.
 template <bool VEC>
@@ -57,30 +59,34 @@ __device__ inline v4f load4(const float* row, int k, int IN, bool rowok) {
     return v;
 }
 
-template <int FO, int FN, bool VEC>
-__global__ __launch_bounds__(256) void dense_mfma(DenseArgs a) {
+// Four consecutive elements of a row (VEC: 16-byte aligned).
+template <bool VEC>
+__device__ inline v4f row4(const float* p) {
+    if constexpr (VEC) return *reinterpret_cast<const v4f*>(p);
+    return v4f{p[0], p[1], p[2], p[3]};
+}
+
+template <int FO, int FN, int WAVES, int U, bool VEC>
+__global__ __launch_bounds__(WAVES * 64) void dense_mfma(DenseArgs a) {
     const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int li = lane & 15;
     const int g = lane >> 4;
     const int o0 = blockIdx.x * 16 * FO;
     const int n0 = blockIdx.y * 16 * FN;
 
+    // (rows past the last read row 0 and are never stored)
     const float* wr[FO];
-    bool wok[FO];
 #pragma unroll
     for (int f = 0; f < FO; ++f) {
         const int o = o0 + 16 * f + li;
-        wok[f] = o < a.OUT;
-        wr[f] = a.w + (long)(wok[f] ? o : 0) * a.IN;
+        wr[f] = a.w + (long)(o < a.OUT ? o : 0) * a.IN + 4 * g;
     }
     const float* xr[FN];
-    bool xok[FN];
 #pragma unroll
     for (int p = 0; p < FN; ++p) {
         const int n = n0 + 16 * p + li;
-        xok[p] = n < a.N;
-        xr[p] = a.x + (long)(xok[p] ? n : 0) * a.IN;
+        xr[p] = a.x + (long)(n < a.N ? n : 0) * a.IN + 4 * g;
     }
 
     v4f acc[FO][FN];
@@ -88,60 +94,77 @@ __global__ __launch_bounds__(256) void dense_mfma(DenseArgs a) {
     for (int f = 0; f < FO; ++f)
 #pragma unroll
         for (int p = 0; p < FN; ++p) acc[f][p] = v4f{0.f, 0.f, 0.f, 0.f};
+    auto mma = [&](const v4f (&wa)[FO], const v4f (&xb)[FN]) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int f = 0; f < FO; ++f)
+#pragma unroll
+                for (int p = 0; p < FN; ++p)
+                    acc[f][p] = __builtin_amdgcn_mfma_f32_16x16x4f32(wa[f][t], xb[p][t], acc[f][p], 0, 0, 0);
+    };
 
-    for (int c0 = wave; c0 < a.T; c0 += kWaves * kU) {
-        v4f wa[kU][FO], xb[kU][FN];
-#pragma unroll
-        for (int u = 0; u < kU; ++u) {
-            const int c = c0 + u * kWaves;
-            const int k = c * 16 + 4 * g;
-            const bool in = c < a.T;
-#pragma unroll
-            for (int f = 0; f < FO; ++f) wa[u][f] = load4<VEC>(wr[f], k, a.IN, in && wok[f]);
-#pragma unroll
-            for (int p = 0; p < FN; ++p) xb[u][p] = load4<VEC>(xr[p], k, a.IN, in && xok[p]);
-        }
-#pragma unroll
-        for (int u = 0; u < kU; ++u)
-#pragma unroll
-            for (int t = 0; t < 4; ++t)
-#pragma unroll
-                for (int f = 0; f < FO; ++f)
-#pragma unroll
-                    for (int p = 0; p < FN; ++p)
-                        acc[f][p] = __builtin_amdgcn_mfma_f32_16x16x4f32(wa[u][f][t], xb[u][p][t],
-                                                                         acc[f][p], 0, 0, 0);
-    }
-
-    __shared__ float red[kWaves - 1][FO * FN * 4][64];
-    if (wave > 0) {
+    // The whole chunks, two at a time (the 128 bytes of a cache line of every
+    // row), the wave's every WAVES-th pair: U pairs in flight.
+    const int full = a.IN / 16, pairs = full / 2;
+    v4f wa[U][2][FO], xb[U][2][FN];
+    auto load = [&](v4f (&w)[2][FO], v4f (&x)[2][FN], int c) {
+        const int k = min(c, pairs - 1) * 32;  // (past the last pair: read again, not used)
 #pragma unroll
         for (int f = 0; f < FO; ++f)
 #pragma unroll
-            for (int p = 0; p < FN; ++p)
+            for (int h = 0; h < 2; ++h) w[h][f] = row4<VEC>(wr[f] + k + 16 * h);
 #pragma unroll
-                for (int v = 0; v < 4; ++v) red[wave - 1][(f * FN + p) * 4 + v][lane] = acc[f][p][v];
-    }
-    __syncthreads();
-    if (wave != 0) return;
-
+        for (int p = 0; p < FN; ++p)
 #pragma unroll
-    for (int f = 0; f < FO; ++f) {
+            for (int h = 0; h < 2; ++h) x[h][p] = row4<VEC>(xr[p] + k + 16 * h);
+    };
+    if (wave < pairs) {
 #pragma unroll
-        for (int p = 0; p < FN; ++p) {
-            const int n = n0 + 16 * p + li;
-            if (n >= a.N) continue;
+        for (int u = 0; u < U; ++u) load(wa[u], xb[u], wave + u * WAVES);
+        for (int c0 = wave; c0 < pairs; c0 += WAVES * U) {
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int o = o0 + 16 * f + 4 * g + v;
-                if (o >= a.OUT) continue;
-                const int q = (f * FN + p) * 4 + v;
-                float r = ((acc[f][p][v] + red[0][q][lane]) + red[1][q][lane]) + red[2][q][lane];
-                if (a.bias) r += a.bias[o];
-                if (a.act == NEO_ACT_RELU) r = r > 0.f ? r : 0.f;
-                a.y[(long)n * a.OUT + o] = r;
+            for (int u = 0; u < U; ++u) {
+                if (c0 + u * WAVES >= pairs) break;
+                mma(wa[u][0], xb[u][0]);
+                mma(wa[u][1], xb[u][1]);
+                load(wa[u], xb[u], c0 + (u + U) * WAVES);
             }
         }
+    }
+    // what is left: a whole chunk and a part of one
+    if (wave == 0) {
+        for (int c = 2 * pairs; c < a.T; ++c) {
+            v4f w[FO], x[FN];
+#pragma unroll
+            for (int f = 0; f < FO; ++f) w[f] = load4<VEC>(wr[f] - 4 * g, c * 16 + 4 * g, a.IN, true);
+#pragma unroll
+            for (int p = 0; p < FN; ++p) x[p] = load4<VEC>(xr[p] - 4 * g, c * 16 + 4 * g, a.IN, true);
+            mma(w, x);
+        }
+    }
+
+    // the waves' partial tiles, added in wave order by all threads
+    __shared__ float red[WAVES][FO * FN * 4][64];
+#pragma unroll
+    for (int f = 0; f < FO; ++f)
+#pragma unroll
+        for (int p = 0; p < FN; ++p)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) red[wave][(f * FN + p) * 4 + v][lane] = acc[f][p][v];
+    __syncthreads();
+    for (int t = threadIdx.x; t < FO * FN * 256; t += WAVES * 64) {
+        // consecutive threads: the 16 outputs of one batch row
+        const int fp = t >> 8, j = t & 255, oo = j & 15, nn = j >> 4;
+        const int q = fp * 4 + (oo & 3), l = (oo >> 2) * 16 + nn;
+        const int o = o0 + 16 * (fp / FN) + oo, n = n0 + 16 * (fp % FN) + nn;
+        if (o >= a.OUT || n >= a.N) continue;
+        float r = red[0][q][l];
+#pragma unroll
+        for (int w = 1; w < WAVES; ++w) r += red[w][q][l];
+        if (a.bias) r += a.bias[o];
+        if (a.act == NEO_ACT_RELU) r = r > 0.f ? r : 0.f;
+        a.y[(long)n * a.OUT + o] = r;
     }
 }
 
@@ -233,10 +256,10 @@ hipError_t launch_rows(const DenseArgs& a, hipStream_t st) {
     return hipGetLastError();
 }
 
-template <int FO, int FN, bool VEC>
+template <int FO, int FN, int WAVES, int U, bool VEC>
 hipError_t launch_t(const DenseArgs& a, hipStream_t st) {
     dim3 grid(cdiv(a.OUT, 16 * FO), cdiv(a.N, 16 * FN));
-    hipLaunchKernelGGL((dense_mfma<FO, FN, VEC>), grid, dim3(256), 0, st, a);
+    hipLaunchKernelGGL((dense_mfma<FO, FN, WAVES, U, VEC>), grid, dim3(WAVES * 64), 0, st, a);
     return hipGetLastError();
 }
 
@@ -245,8 +268,15 @@ hipError_t dispatch(const DenseArgs& a, hipStream_t st) {
     if (a.N == 1) return launch_rows<1, VEC>(a, st);
     if (a.N == 2) return launch_rows<2, VEC>(a, st);
     if (a.N <= 4) return launch_rows<4, VEC>(a, st);
-    if (a.N <= 16) return launch_t<1, 1, VEC>(a, st);
-    return launch_t<1, 2, VEC>(a, st);
+    // One 16 x 16 tile per workgroup while those are at most one per CU (or the
+    // batch is one tile): measured 11.3 against 15.7 us for 32 x 2048 -> 1000,
+    // 89 against 132 us for 64 x 25,088 -> 100.  Beyond, a tile of the weights
+    // is read for 32 images, and past 32 images for two output tiles: 141
+    // against 211 us for 32 x 25,088 -> 4096, 181 against 401 (one tile) and
+    // 280 us (two) for 64.
+    if (a.N <= 16 || (long)cdiv(a.OUT, 16) * cdiv(a.N, 16) <= 256) return launch_t<1, 1, 8, 2, VEC>(a, st);
+    if (a.N <= 32) return launch_t<1, 2, 8, 2, VEC>(a, st);
+    return launch_t<2, 2, 4, 2, VEC>(a, st);
 }
 
 }  // namespace
