@@ -1,6 +1,11 @@
 // Blocked convolution on fp32 MFMA (gfx950): launch configuration, cost model
 // and launcher.  The kernels are in conv_kernel.h; this file instantiates the
 // NCHW16c -> NCHW16c family, conv_xy.hip every other pair of blocks.
+#include <array>
+#include <map>
+#include <mutex>
+#include <new>
+
 #include "conv_h2.h"
 
 namespace neo {
@@ -197,7 +202,9 @@ constexpr double kH2Line = 1.4;
 
 }  // namespace
 
-ConvConfig choose_conv_config(const ConvShape& s) {
+namespace {
+
+ConvConfig model_conv_config(const ConvShape& s) {
     double tile_us = 0;
     ConvConfig best = choose_tile_config(s, &tile_us);
     double best_us = kH2Line * tile_us;
@@ -216,6 +223,31 @@ ConvConfig choose_conv_config(const ConvShape& s) {
                 }
             }
     return best;
+}
+
+// The models' choices of the last shapes asked for: evaluating them takes a few
+// microseconds, about as long as a small layer runs.
+constexpr size_t kMaxChoices = 1024;
+std::mutex g_choices_mu;
+std::map<std::array<int, 13>, ConvConfig> g_choices;
+
+}  // namespace
+
+ConvConfig choose_conv_config(const ConvShape& s) {
+    const std::array<int, 13> key{s.N, s.C, s.H, s.W, s.K, s.R, s.S, s.sh, s.sw, s.ph, s.pw, s.gap, s.yb};
+    {
+        std::lock_guard<std::mutex> lk(g_choices_mu);
+        const auto it = g_choices.find(key);
+        if (it != g_choices.end()) return it->second;
+    }
+    const ConvConfig c = model_conv_config(s);
+    try {
+        std::lock_guard<std::mutex> lk(g_choices_mu);
+        if (g_choices.size() >= kMaxChoices) g_choices.clear();
+        g_choices[key] = c;
+    } catch (const std::bad_alloc&) {  // kept for speed only
+    }
+    return c;
 }
 
 size_t conv_workspace_bytes(const ConvShape& s, const ConvConfig& c) {

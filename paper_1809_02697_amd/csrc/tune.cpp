@@ -37,14 +37,30 @@ struct Entry {
 std::mutex g_mu;
 std::map<Key, Entry> g_db;
 
+// The current device's architecture name, asked of the runtime once per device
+// (the query takes microseconds, and every standalone call looks its shape up).
+constexpr int kMaxArchDevices = 64;
+std::mutex g_arch_mu;
+std::string g_arch[kMaxArchDevices];
+
 std::string device_arch() {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) return "unknown";
+    const bool keep = dev >= 0 && dev < kMaxArchDevices;
+    if (keep) {
+        std::lock_guard<std::mutex> lk(g_arch_mu);
+        if (!g_arch[dev].empty()) return g_arch[dev];
+    }
     hipDeviceProp_t prop;
     if (hipGetDeviceProperties(&prop, dev) != hipSuccess) return "unknown";
     std::string a = prop.gcnArchName;
     const size_t colon = a.find(':');
-    return colon == std::string::npos ? a : a.substr(0, colon);
+    if (colon != std::string::npos) a = a.substr(0, colon);
+    if (keep) {
+        std::lock_guard<std::mutex> lk(g_arch_mu);
+        g_arch[dev] = a;
+    }
+    return a;
 }
 
 // The input and output blocks of a stored workload are ones the kernel takes.
@@ -104,6 +120,10 @@ std::vector<ConvConfig> stream_candidates(const ConvShape& s) {
 }  // namespace
 
 bool tuned_config(const ConvShape& s, bool wmfma, ConvConfig* out) {
+    {
+        std::lock_guard<std::mutex> lk(g_mu);
+        if (g_db.empty()) return false;
+    }
     const std::string arch = device_arch();
     std::lock_guard<std::mutex> lk(g_mu);
     auto it = g_db.find(key_of(s, wmfma, arch));
