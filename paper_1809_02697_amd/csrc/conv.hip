@@ -16,10 +16,10 @@ static_assert(kMaxGroup == kMaxGroupConvs, "group size");
 
 extern template hipError_t conv_detail::dispatch_all<true>(const ConvConfig&, int, bool, bool,
                                                            const ConvArgs&, hipStream_t);
-extern template hipError_t conv_detail::dispatch_h2<false, false>(const ConvConfig&, int, const H2Args&, hipStream_t);
-extern template hipError_t conv_detail::dispatch_h2<false, true>(const ConvConfig&, int, const H2Args&, hipStream_t);
-extern template hipError_t conv_detail::dispatch_h2<true, false>(const ConvConfig&, int, const H2Args&, hipStream_t);
-extern template hipError_t conv_detail::dispatch_h2<true, true>(const ConvConfig&, int, const H2Args&, hipStream_t);
+extern template hipError_t conv_detail::dispatch_h2<false, false>(const ConvConfig&, int, bool, const H2Args&, hipStream_t);
+extern template hipError_t conv_detail::dispatch_h2<false, true>(const ConvConfig&, int, bool, const H2Args&, hipStream_t);
+extern template hipError_t conv_detail::dispatch_h2<true, false>(const ConvConfig&, int, bool, const H2Args&, hipStream_t);
+extern template hipError_t conv_detail::dispatch_h2<true, true>(const ConvConfig&, int, bool, const H2Args&, hipStream_t);
 
 int conv_group(const ConvShape& s, const ConvConfig& c) {
     if (conv_small_c(s)) return 1;
@@ -43,7 +43,11 @@ struct H2Geometry {
     long tiles;
 };
 
-constexpr int kH2MaxPatch = 512;
+constexpr int kH2MaxPatch = 512, kH2MaxSmallPatch = 1536;
+
+// Kernel columns that a patch row holds past its pixels' first: on the
+// small-channel path whole groups of four.
+int h2_columns(const ConvShape& s) { return conv_small_c(s) ? 4 * cdiv(s.S, 4) : s.S; }
 
 // Whole rows of consecutive pixels (which may run over several images), or
 // blocks of th x tw pixels of one image, whichever costs least: per channel
@@ -52,14 +56,17 @@ constexpr int kH2MaxPatch = 512;
 // fits.
 bool h2_geometry(const ConvShape& s, int P, H2Geometry* out) {
     const long M = (long)s.N * s.OH * s.OW;
-    if (s.R == 1 && s.S == 1) {
+    const bool small = conv_small_c(s);
+    const int S = h2_columns(s);
+    if (s.R == 1 && s.S == 1 && !small) {
         *out = H2Geometry{kH2Point, 0, 0, 1, P, (M + P - 1) / P};
         return true;
     }
     double best = 1e300;
     auto consider = [&](int kind, int ltw, int th, long PW, long rows, long tiles) {
-        if (PW * rows > kH2MaxPatch) return;
-        const double cost = (double)tiles * (3.0 * P * s.R * s.S + 1.5 * (double)(PW * rows));
+        if (PW * rows > (small ? kH2MaxSmallPatch : kH2MaxPatch)) return;
+        const double cost = small ? (double)tiles * (3.0 * P * s.R * S / 4 + 0.4 * (double)(PW * rows))
+                                  : (double)tiles * (3.0 * P * s.R * s.S + 1.5 * (double)(PW * rows));
         if (cost < best) {
             best = cost;
             *out = H2Geometry{kind, ltw, th, (int)PW, (int)(PW * rows), tiles};
@@ -69,18 +76,20 @@ bool h2_geometry(const ConvShape& s, int P, H2Geometry* out) {
         // output rows that P consecutive pixels touch, and images those rows lie in
         const long nr = std::min<long>((P - 2) / s.OW + 2, (long)s.N * s.OH);
         const long ni = std::min<long>(nr < 2 ? 1 : (nr - 2) / s.OH + 2, s.N);
-        consider(kH2Rows, 0, 0, (long)(s.OW - 1) * s.sw + s.S, nr * s.sh + ni * std::max(s.R - s.sh, 0), (M + P - 1) / P);
+        consider(kH2Rows, 0, 0, (long)(s.OW - 1) * s.sw + S, nr * s.sh + ni * std::max(s.R - s.sh, 0), (M + P - 1) / P);
     }
     for (int ltw = 2; (1 << ltw) <= P; ++ltw) {
         const int tw = 1 << ltw, th = P / tw;
-        consider(kH2Block, ltw, th, (long)(tw - 1) * s.sw + s.S, (long)(th - 1) * s.sh + s.R,
+        consider(kH2Block, ltw, th, (long)(tw - 1) * s.sw + S, (long)(th - 1) * s.sh + s.R,
                  (long)s.N * cdiv(s.OH, th) * cdiv(s.OW, tw));
     }
     return best < 1e300;
 }
 
-// Patch pixels / 64 that the kernel is instantiated for.
-int h2_patch_blocks(const H2Geometry& g) {
+// Patch pixels / 64 (/ 256 on the small-channel path) that the kernel is
+// instantiated for.
+int h2_patch_blocks(const ConvShape& s, const H2Geometry& g) {
+    if (conv_small_c(s)) return cdiv(g.patch, 512) * 2;
     const int n = cdiv(g.patch, 64);
     return g.kind == kH2Point ? n : n <= 2 ? 2 : n <= 3 ? 3 : n <= 5 ? 5 : 8;
 }
@@ -92,7 +101,7 @@ int h2_pixels(const ConvConfig& c) { return 32 * c.fp * (kH2Waves / c.fk); }
 bool conv_h2_config_valid(const ConvShape& s, const ConvConfig& c) {
     // (the folded global pool needs the tile kernel's epilogue)
     if (!conv_h2(c) || !(c.fk == 2 || c.fk == 4) || !(c.fp == 2 || c.fp == 4) || c.split < 1 || c.split > 64 ||
-        s.gap || conv_small_c(s))
+        s.gap || (conv_small_c(s) && c.split > 1))
         return false;
     H2Geometry g;
     return h2_geometry(s, h2_pixels(c), &g) && g.tiles * cdiv(cdiv(s.K, s.yb) * s.yb, 32 * c.fk) * c.split < (1L << 30) &&
@@ -101,16 +110,21 @@ bool conv_h2_config_valid(const ConvShape& s, const ConvConfig& c) {
 
 int conv_h2_chunks(const ConvShape& s, const ConvConfig& c) {
     const int CB = cdiv(s.C, 16);
-    return s.R == 1 && s.S == 1 ? cdiv(CB, h2_blocks(h2_pixels(c) / 64)) : CB;
+    return s.R == 1 && s.S == 1 && !conv_small_c(s) ? cdiv(CB, h2_blocks(h2_pixels(c) / 64)) : CB;
+}
+
+// Steps of the whole reduction.
+static int h2_filter_steps(const ConvShape& s) {
+    return conv_small_c(s) ? s.R * cdiv(s.S, 4) : cdiv(s.C, 16) * s.R * s.S;
 }
 
 long h2_filter_floats(const ConvShape& s) {
     const long kb = cdiv(cdiv(s.K, 16), 2);
-    return kb * cdiv(s.C, 16) * s.R * s.S * 512 + kb * 32;
+    return kb * h2_filter_steps(s) * 512 + kb * 32;
 }
 
 hipError_t launch_h2_filter(const ConvShape& s, const float* w, float* out, hipStream_t st) {
-    const int KB = cdiv(s.K, 16), steps = cdiv(s.C, 16) * s.R * s.S;
+    const int KB = cdiv(s.K, 16), steps = h2_filter_steps(s);
     return launch_h2_split(w, KB, steps, out, reinterpret_cast<int*>(out + (long)cdiv(KB, 2) * steps * 512), st);
 }
 
@@ -178,10 +192,10 @@ namespace {
 double h2_time_us(const ConvShape& s, const ConvConfig& c) {
     H2Geometry g;
     if (!conv_h2_config_valid(s, c) || !h2_geometry(s, h2_pixels(c), &g)) return 1e30;
-    const int CB = cdiv(s.C, 16), ni = h2_patch_blocks(g), uc = g.kind == kH2Point ? h2_blocks(ni) : 1;
+    const int CB = cdiv(s.C, 16), ni = h2_patch_blocks(s, g), uc = g.kind == kH2Point ? h2_blocks(ni) : 1;
     const int chunks = cdiv(conv_h2_chunks(s, c), c.split);
-    const double steps = (double)std::min(uc, CB) * s.R * s.S, items = uc * ni;
-    const long lds = 2L * uc * 4 * (64 * ni + 4) * 16 + 2048;
+    const double steps = conv_small_c(s) ? h2_filter_steps(s) : (double)std::min(uc, CB) * s.R * s.S, items = uc * ni;
+    const long lds = 2048 + (conv_small_c(s) ? 16L * (256 * ni + 4) : 2L * uc * 4 * (64 * ni + 4) * 16);
     const double occ = (double)std::max<long>(1, std::min<long>(c.fp == 4 ? 2 : 3, 163840 / lds));
     const double chain = chunks * (steps * (133.0 + 185.0 * c.fp) + 337.0 * items) + 10400.0;
     const double share = chunks * (steps * (181.0 + 96.0 * c.fp) + 264.0 * items) + 5600.0;
@@ -346,9 +360,9 @@ hipError_t launch_conv2d(const ConvShape& s, const ConvConfig& c, const float* x
         h.w32_bytes = a.w_bytes;
         h.wexp = nullptr;
         if (wmfma) {
-            const long kb = cdiv(a.KB, 2);
-            a.w_bytes = (int)(kb * a.CB * a.RS * 2048);
-            h.wexp = reinterpret_cast<const int*>(wh2 + kb * a.CB * a.RS * 512);
+            const long blocks = (long)cdiv(a.KB, 2) * h2_filter_steps(s);
+            a.w_bytes = (int)(blocks * 2048);
+            h.wexp = reinterpret_cast<const int*>(wh2 + blocks * 512);
         }
         h.kind = g.kind;
         h.ltw = g.ltw;
@@ -360,10 +374,10 @@ hipError_t launch_conv2d(const ConvShape& s, const ConvConfig& c, const float* x
         const int tx = g.kind == kH2Block ? cdiv(s.OW, 1 << g.ltw) : 1;
         h.div_tx = make_fastdiv((unsigned)tx);
         h.div_tpi = make_fastdiv((unsigned)(g.kind == kH2Block ? tx * cdiv(s.OH, g.th) : 1));
-        const int n = h2_patch_blocks(g);
-        const bool xy = s.xb != 16 || s.yb != 16;
-        if (wmfma) return xy ? dispatch_h2<true, true>(c, n, h, st) : dispatch_h2<true, false>(c, n, h, st);
-        return xy ? dispatch_h2<false, true>(c, n, h, st) : dispatch_h2<false, false>(c, n, h, st);
+        const int n = h2_patch_blocks(s, g);
+        const bool xy = s.xb != 16 || s.yb != 16, small = conv_small_c(s);
+        if (wmfma) return xy ? dispatch_h2<true, true>(c, n, small, h, st) : dispatch_h2<true, false>(c, n, small, h, st);
+        return xy ? dispatch_h2<false, true>(c, n, small, h, st) : dispatch_h2<false, false>(c, n, small, h, st);
     }
     if (!conv_config_valid(c) || !conv_blocks_valid(s)) return hipErrorInvalidValue;
     if (s.gap && s.N != 1) return hipErrorInvalidValue;

@@ -42,6 +42,9 @@
 //     keep the filter as converted terms in that order (h2_split_filter), a
 //     linear stream of 2 KB per step and 32 channels; a filter in float32
 //     KCRS[16]c[16]k is converted as it is used.
+// Inputs of at most four channels (network stems) keep four channels per patch
+// pixel, and a step is a kernel row and four of its columns: lane (i, g) reads
+// columns 2 g and 2 g + 1 of its pixel's window, two neighbouring patch pixels.
 // The reduction runs over chunks, then the blocks of a chunk, then the kernel
 // entries: the filter's own order.  It may be split over workgroups by
 // chunks (partials, then split_reduce).
@@ -203,10 +206,25 @@ struct H2Tile {
     }
 };
 
+// Small-channel path: channels 0..3 of the pixel at byte offset off.
+template <bool XY>
+__device__ inline v4f h2_small_x(const ConvArgs& a, __amdgpu_buffer_rsrc_t xr, unsigned off) {
+    if constexpr (XY) {
+        if (a.xb == 1) {  // NCHW: the channels lie a plane apart; the rest are 0
+            const int plane = __builtin_amdgcn_readfirstlane(a.H * a.W * 4);
+            v4f v;
+#pragma unroll
+            for (int t = 0; t < 4; ++t) v[t] = t < a.XB ? ld1(xr, off, t * plane, 0) : 0.f;
+            return v;
+        }
+    }
+    return ld4(xr, off, 0, 0);
+}
+
 // The tile of one wave again in float32: chunk blocks [c_lo, c_hi) of the
 // reduction, operands straight from memory (eight elements of a unit per
 // lane, v_mfma_f32_32x32x2f32).
-template <int NP, bool PRE, bool XY>
+template <int NP, bool PRE, bool XY, bool SMALL>
 __device__ inline void h2_again(const H2Args& h, const H2Tile& t, int kb, int p0, int c_lo, int c_hi, int lane,
                                 v16f (&acc)[NP]) {
     const ConvArgs& a = h.a;
@@ -235,21 +253,31 @@ __device__ inline void h2_again(const H2Args& h, const H2Tile& t, int kb, int p0
 #pragma unroll 1
         for (int r = 0; r < a.R; ++r)
 #pragma unroll 1
-            for (int s = 0; s < a.S; ++s) {
+            for (int s = 0; s < (SMALL ? a.U : a.S); ++s) {
                 v4f wv[2], xv[NP][2];
 #pragma unroll
                 for (int e = 0; e < 2; ++e) {
+                    const int sc = SMALL ? 4 * s + 2 * g + e : s;  // kernel column
 #pragma unroll
                     for (int p = 0; p < NP; ++p) {
-                        const int ih = ih0[p] + r, iw = iw0[p] + s;
-                        const bool ok = in[p] && (unsigned)ih < (unsigned)a.H && (unsigned)iw < (unsigned)a.W;
-                        const int at = ((n[p] * xblocks<XY>(a) * a.H + ih) * a.W + iw) * xpb_of<XY>(a) +
-                                       (XY ? xgroup(a, cb) : cb * a.H * a.W * 64) + 32 * g + 16 * e;
-                        xv[p][e] = ld4(xr, ok ? (unsigned)at : kOutOfRange, 0, 0);
+                        const int ih = ih0[p] + r, iw = iw0[p] + sc;
+                        const bool ok =
+                            in[p] && sc < a.S && (unsigned)ih < (unsigned)a.H && (unsigned)iw < (unsigned)a.W;
+                        const int at = ((n[p] * xblocks<XY>(a) * a.H + ih) * a.W + iw) * xpb_of<XY>(a);
+                        if constexpr (SMALL)
+                            xv[p][e] = h2_small_x<XY>(a, xr, ok ? (unsigned)at : kOutOfRange);
+                        else
+                            xv[p][e] = ld4(xr, ok ? (unsigned)(at + (XY ? xgroup(a, cb) : cb * a.H * a.W * 64) + 32 * g + 16 * e)
+                                                  : kOutOfRange, 0, 0);
                     }
-                    const int block = ((k16 * a.CB + cb) * a.RS + r * a.S + s) * 1024;
+                    const int block = SMALL && PRE ? ((k16 * a.R + r) * a.U + s) * 1024
+                                                   : ((k16 * a.CB + cb) * a.RS + r * a.S + sc) * 1024;
                     if constexpr (PRE) {
                         wv[e] = ld4(wr, kok ? (unsigned)(block + ((2 * g + e) * 16 + li) * 16) : kOutOfRange, 0, 0);
+                    } else if constexpr (SMALL) {
+#pragma unroll
+                        for (int q = 0; q < 4; ++q)
+                            wv[e][q] = ld1(wr, kok && sc < a.S ? (unsigned)(block + (q * 16 + li) * 4) : kOutOfRange, 0, 0);
                     } else {
 #pragma unroll
                         for (int q = 0; q < 4; ++q)
@@ -265,12 +293,15 @@ __device__ inline void h2_again(const H2Args& h, const H2Tile& t, int kb, int p0
             }
 }
 
-// NI: patch pixels per 64 (the patch has at most 64 NI pixels).
-template <int NP, int WK, int NI, int UC, bool PRE, bool XY>
+// NI: patch pixels per 64 (the patch has at most 64 NI pixels), per 256 on the
+// small-channel path.
+template <int NP, int WK, int NI, int UC, bool PRE, bool XY, bool SMALL>
 __global__ __launch_bounds__(64 * kH2Waves, 2) void conv2d_h2(H2Args h) {
     constexpr int WP = kH2Waves / WK;
-    constexpr int kPlane = 64 * NI + 4;  // (a half's pixels; the 4 keep the halves' 8-byte writes in different banks)
-    __shared__ v8h xl[2][UC][2][2][kPlane];
+    // v8h (small-channel path: v4h) of a plane; the 4 keep the halves' 8-byte
+    // writes in different banks
+    constexpr int kPlane = (SMALL ? 256 : 64) * NI + 4;
+    __shared__ v8h xl[SMALL ? 1 : 2][SMALL ? 1 : UC][2][SMALL ? 1 : 2][SMALL ? kPlane / 2 : kPlane];
     __shared__ unsigned top[kH2Waves];
     // for the epilogue: image and position of the tile's pixels, its channels'
     // bias and scale exponents (loaded now: at the end each load would wait
@@ -319,11 +350,12 @@ __global__ __launch_bounds__(64 * kH2Waves, 2) void conv2d_h2(H2Args h) {
         }
     }
 
-    // ---- input: thread t loads quad t % 4 of patch pixels t / 4 + 64 j
-    const int xq = threadIdx.x & 3, xp = threadIdx.x >> 2;
+    // ---- input: thread t loads quad t % 4 of patch pixels t / 4 + 64 j (the
+    // small-channel path: pixels t + 256 j)
+    const int xq = threadIdx.x & 3, xp = SMALL ? threadIdx.x : threadIdx.x >> 2;
     unsigned xoff[NI];
 #pragma unroll
-    for (int j = 0; j < NI; ++j) xoff[j] = tile.input<XY>(h, xp + 64 * j) + 16 * xq;
+    for (int j = 0; j < NI; ++j) xoff[j] = tile.input<XY>(h, xp + (SMALL ? 256 : 64) * j) + (SMALL ? 0 : 16 * xq);
     const int dx = __builtin_amdgcn_readfirstlane(a.H * a.W * 64);
     auto load_x = [&](v4f (&v)[UC][NI], int cb0) {
 #pragma unroll
@@ -332,7 +364,7 @@ __global__ __launch_bounds__(64 * kH2Waves, 2) void conv2d_h2(H2Args h) {
             const int cb = min(cb0 + c, c_hi - 1);
             const int so = __builtin_amdgcn_readfirstlane(XY ? xgroup(a, cb) : cb * dx);
 #pragma unroll
-            for (int j = 0; j < NI; ++j) v[c][j] = ld4(xr, xoff[j], so, 0);
+            for (int j = 0; j < NI; ++j) v[c][j] = SMALL ? h2_small_x<XY>(a, xr, xoff[j]) : ld4(xr, xoff[j], so, 0);
         }
     };
     auto max_x = [&](const v4f (&v)[UC][NI], float m) {
@@ -343,41 +375,63 @@ __global__ __launch_bounds__(64 * kH2Waves, 2) void conv2d_h2(H2Args h) {
         return m;
     };
 
-    // ---- filter: a step is one channel block at one kernel entry, in the
-    // filter's own order
-    const int f_lo = __builtin_amdgcn_readfirstlane(c_lo * a.RS), f_hi = __builtin_amdgcn_readfirstlane(c_hi * a.RS);
+    // ---- filter: a step is one channel block at one kernel entry, in its
+    // own order (small-channel path: four columns of a kernel row)
+    const int per_block = SMALL ? a.R * a.U : a.RS;
+    const int f_lo = __builtin_amdgcn_readfirstlane(c_lo * per_block);
+    const int f_hi = __builtin_amdgcn_readfirstlane(c_hi * per_block);
     const int li = lane & 15, k16 = 2 * kb + ((lane >> 4) & 1);
-    const unsigned woff = PRE ? (2 * kb < a.KB ? (unsigned)(kb * a.CB * a.RS * 2048 + lane * 16) : kOutOfRange)
-                              : (k16 < a.KB ? (unsigned)(k16 * a.CB * a.RS * 1024 + (lane >> 5) * 512 + li * 4)
+    const unsigned woff = PRE ? (2 * kb < a.KB ? (unsigned)(kb * a.CB * per_block * 2048 + lane * 16) : kOutOfRange)
+                              : (k16 < a.KB ? (unsigned)(k16 * a.CB * a.RS * 1024 + li * 4 +
+                                                         (SMALL ? (lane >> 5) * 2048 : (lane >> 5) * 512))
                                             : kOutOfRange);
     constexpr int kStep = PRE ? 2048 : 1024;
     const int w_end = __builtin_amdgcn_readfirstlane((f_hi - 1) * kStep);
     int w_at = __builtin_amdgcn_readfirstlane(f_lo * kStep);  // the next step's block (stays at the last one)
+    int w_r = 0, w_u = 0;  // small-channel float32 filter: the next step's row and column group
     auto load_w = [&](v4f (&v)[2], int so) {
         if constexpr (PRE) {
             v[0] = ld4(wr, woff, so, 0);
             v[1] = ld4(wr, woff, so, 1024);
+        } else if constexpr (SMALL) {
+            // channels 0..3 of columns 4 u + 2 g + e: blocks of their own
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                const bool ok = 4 * w_u + 2 * (lane >> 5) + e < a.S;
+#pragma unroll
+                for (int t = 0; t < 4; ++t) v[e][t] = ld1(wr, ok ? woff : kOutOfRange, so, e * 1024 + t * 64);
+            }
         } else {
 #pragma unroll
             for (int t = 0; t < 8; ++t) v[t / 4][t % 4] = ld1(wr, woff, so, t * 64);
         }
     };
     auto next_w = [&](v4f (&v)[2]) {
-        load_w(v, w_at);
-        w_at = __builtin_amdgcn_readfirstlane(min(w_at + kStep, w_end));
+        if constexpr (SMALL && !PRE) {
+            load_w(v, __builtin_amdgcn_readfirstlane((w_r * a.S + 4 * w_u) * 1024));
+            const bool row = w_u + 1 == a.U, last = row && w_r + 1 == a.R;
+            w_u = __builtin_amdgcn_readfirstlane(last ? w_u : row ? 0 : w_u + 1);
+            w_r = __builtin_amdgcn_readfirstlane(row && !last ? w_r + 1 : w_r);
+        } else {
+            load_w(v, w_at);
+            w_at = __builtin_amdgcn_readfirstlane(min(w_at + kStep, w_end));
+        }
     };
 
     v4f wv[kH2Ring][2], xv[UC][NI];
     // ---- scales
     int ew = 0, ex;
     {
-        v4f mid[UC][NI], wmid[2];
-        load_x(mid, (c_lo + c_hi) / 2);
-        if constexpr (!PRE) load_w(wmid, __builtin_amdgcn_readfirstlane((f_lo + f_hi) / 2 * kStep));
+        v4f mid = v4f{0.f, 0.f, 0.f, 0.f}, wmid[2] = {mid, mid};
+        if constexpr (!SMALL) {
+            const int cm = (c_lo + c_hi) / 2;
+            mid = ld4(xr, xoff[NI / 2], __builtin_amdgcn_readfirstlane(XY ? xgroup(a, cm) : cm * dx), 0);
+            if constexpr (!PRE) load_w(wmid, __builtin_amdgcn_readfirstlane((f_lo + f_hi) / 2 * kStep));
+        }
         load_x(xv, c_lo);
 #pragma unroll
         for (int d = 0; d < kH2Ring; ++d) next_w(wv[d]);
-        const float mx = h2_wave_max(max_x(xv, max_x(mid, 0.f)));
+        const float mx = h2_wave_max(max_x(xv, h2_max(mid, 0.f)));
         if (lane == 0) top[wave] = __float_as_uint(mx);
         if constexpr (!PRE) {
             float mw = h2_max(wmid[0], h2_max(wmid[1], 0.f));
@@ -401,13 +455,19 @@ __global__ __launch_bounds__(64 * kH2Waves, 2) void conv2d_h2(H2Args h) {
                 v4h t[2];
                 h2_terms(xv[c][j], sclx, sclx2, t[0], t[1]);
 #pragma unroll
-                for (int e = 0; e < 2; ++e)
-                    reinterpret_cast<v4h*>(&xl[buf][c][e][xq >> 1][xp + 64 * j])[xq & 1] = t[e];
+                for (int e = 0; e < 2; ++e) {
+                    if constexpr (SMALL)
+                        reinterpret_cast<v4h*>(&xl[0][0][e][0][0])[xp + 256 * j] = t[e];
+                    else
+                        reinterpret_cast<v4h*>(&xl[buf][c][e][xq >> 1][xp + 64 * j])[xq & 1] = t[e];
+                }
             }
     };
 
     v16f acc[NP], accl[NP];
-    int at[NP];  // the lane's 16 bytes at its pixel's first window entry (v8h index from a term's plane)
+    // the lane's 16 bytes at its pixel's first window entry: v8h index from a
+    // term's plane (small-channel path: v4h index of columns 2 g, 2 g + 1)
+    int at[NP];
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
         const int q = p0 + p * 32 + (lane & 31);
@@ -415,7 +475,7 @@ __global__ __launch_bounds__(64 * kH2Waves, 2) void conv2d_h2(H2Args h) {
         tile.pixel(h, q, n, pix, base);
         where[0][q] = n;
         where[1][q] = pix;
-        at[p] = (lane >> 5) * kPlane + (pix >= 0 ? base : 0);
+        at[p] = (lane >> 5) * (SMALL ? 2 : kPlane) + (pix >= 0 ? base : 0);
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
             acc[p][v] = 0.f;
@@ -434,34 +494,44 @@ __global__ __launch_bounds__(64 * kH2Waves, 2) void conv2d_h2(H2Args h) {
     }
     const v8h* const x0 = &xl[0][0][0][0][0];
     constexpr int kBlock = 4 * kPlane, kBuffer = UC * kBlock;
+    auto read = [&](int i, int e) {  // term e at index i
+        if constexpr (SMALL) {
+            const v4h* q = reinterpret_cast<const v4h*>(x0) + i + e * kPlane;
+            return h2_join(q[0], q[1]);
+        } else {
+            return x0[i + e * 2 * kPlane];
+        }
+    };
     stage(0);
-    load_x(xv, c_lo + UC);
+    if constexpr (!SMALL) load_x(xv, c_lo + UC);
     __syncthreads();
 #pragma unroll
-    for (int p = 0; p < NP; ++p) xh[0][p] = x0[at[p]];
+    for (int p = 0; p < NP; ++p) xh[0][p] = read(at[p], 0);
     // off: this step's input from the lane's first (a chunk of one block walks
     // the kernel entries, a pointwise chunk its blocks); left: steps of the chunk
-    const int per_chunk = UC > 1 ? UC : __builtin_amdgcn_readfirstlane(a.RS);
-    const int row_skip = __builtin_amdgcn_readfirstlane(h.PW - a.S);
-    int buf = 0, off = 0, s = a.S, left = per_chunk, cb = c_lo;
+    const int per_chunk = UC > 1 ? UC : __builtin_amdgcn_readfirstlane(per_block);
+    const int columns = SMALL ? a.U : a.S;  // steps of a kernel row
+    constexpr int kColumn = SMALL ? 4 : 1;
+    const int row_skip = __builtin_amdgcn_readfirstlane(h.PW - kColumn * columns);
+    int buf = 0, off = 0, s = columns, left = per_chunk, cb = c_lo;
     for (int f0 = f_lo; f0 < f_hi; f0 += kH2Ring) {
 #pragma unroll
         for (int d = 0; d < kH2Ring; ++d) {
             if (f0 + d >= f_hi) break;
 #pragma unroll
-            for (int p = 0; p < NP; ++p) xlo[p] = x0[at[p] + off + 2 * kPlane];
+            for (int p = 0; p < NP; ++p) xlo[p] = read(at[p] + off, 1);
             if constexpr (UC > 1) {
                 off += kBlock;
             } else {
                 const bool row = --s == 0;
-                off += row ? row_skip + 1 : 1;
-                s = row ? a.S : s;
+                off += row ? row_skip + kColumn : kColumn;
+                s = row ? columns : s;
             }
             const bool swap = --left == 0;
             off = swap ? 0 : off;
             // (the chunk's last step reads its first again, in range and unused)
 #pragma unroll
-            for (int p = 0; p < NP; ++p) xh[(d + 1) & 1][p] = x0[at[p] + off];
+            for (int p = 0; p < NP; ++p) xh[(d + 1) & 1][p] = read(at[p] + off, 0);
             v8h w[2];
             if constexpr (PRE) {
                 w[0] = __builtin_bit_cast(v8h, wv[d][0]);
@@ -482,7 +552,7 @@ __global__ __launch_bounds__(64 * kH2Waves, 2) void conv2d_h2(H2Args h) {
             for (int p = 0; p < NP; ++p)
                 accl[p] = __builtin_amdgcn_mfma_f32_32x32x16_f16(w[0], xlo[p], accl[p], 0, 0, 0);
             next_w(wv[d]);
-            if (swap && f0 + d + 1 < f_hi) {
+            if (!SMALL && swap && f0 + d + 1 < f_hi) {
                 left = per_chunk;
                 cb += UC;
                 buf ^= 1;
@@ -491,7 +561,7 @@ __global__ __launch_bounds__(64 * kH2Waves, 2) void conv2d_h2(H2Args h) {
                 __syncthreads();
                 off = buf ? kBuffer : 0;
 #pragma unroll
-                for (int p = 0; p < NP; ++p) xh[(d + 1) & 1][p] = x0[at[p] + off];
+                for (int p = 0; p < NP; ++p) xh[(d + 1) & 1][p] = read(at[p] + off, 0);
             }
         }
     }
@@ -506,7 +576,7 @@ __global__ __launch_bounds__(64 * kH2Waves, 2) void conv2d_h2(H2Args h) {
             bad = __builtin_fmaf(acc[p][v], 0.f, bad);
         }
     const bool again = __any(bad != bad);
-    if (again) h2_again<NP, PRE, XY>(h, tile, kb, p0, c_lo, c_hi, lane, acc);
+    if (again) h2_again<NP, PRE, XY, SMALL>(h, tile, kb, p0, c_lo, c_hi, lane, acc);
     // Accumulator element 4 j + v of lane (i, g): channel 8 j + 4 g + v of the
     // block, pixel i.  Every operand of the epilogue is loaded before the first
     // store: a load after a store waits for its own round trip.
@@ -574,11 +644,11 @@ __global__ __launch_bounds__(64 * kH2Waves, 2) void conv2d_h2(H2Args h) {
     }
 }
 
-template <int NP, int WK, int NI, int UC, bool PRE, bool XY>
+template <int NP, int WK, int NI, int UC, bool PRE, bool XY, bool SMALL = false>
 hipError_t launch_h2_t(const H2Args& h, hipStream_t st) {
     const ConvArgs& a = h.a;
     const int wgs = a.div_npx.d * a.div_nkb.d * a.split;
-    hipLaunchKernelGGL((conv2d_h2<NP, WK, NI, UC, PRE, XY>), dim3(wgs), dim3(64 * kH2Waves), 0, st, h);
+    hipLaunchKernelGGL((conv2d_h2<NP, WK, NI, UC, PRE, XY, SMALL>), dim3(wgs), dim3(64 * kH2Waves), 0, st, h);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || a.split == 1) return e;
     const long total = (long)a.N * a.KBk * a.OH * a.OW * 4;
@@ -587,9 +657,18 @@ hipError_t launch_h2_t(const H2Args& h, hipStream_t st) {
     return hipGetLastError();
 }
 
-// ni: patch pixels / 64 (a pointwise layer's are its tile's).
+// ni: patch pixels / 64 (a pointwise layer's are its tile's), / 256 on the
+// small-channel path.
 template <int NP, int WK, bool PRE, bool XY>
-hipError_t dispatch_h2_patch(int ni, const H2Args& h, hipStream_t st) {
+hipError_t dispatch_h2_patch(int ni, bool small, const H2Args& h, hipStream_t st) {
+    if (small) {
+        switch (ni) {
+            case 2: return launch_h2_t<NP, WK, 2, 1, PRE, XY, true>(h, st);
+            case 4: return launch_h2_t<NP, WK, 4, 1, PRE, XY, true>(h, st);
+            case 6: return launch_h2_t<NP, WK, 6, 1, PRE, XY, true>(h, st);
+            default: return hipErrorInvalidValue;
+        }
+    }
     constexpr int kOwn = NP * (kH2Waves / WK) / 2;
     if (h.kind == kH2Point) return launch_h2_t<NP, WK, kOwn, h2_blocks(kOwn), PRE, XY>(h, st);
     switch (ni) {
@@ -603,12 +682,12 @@ hipError_t dispatch_h2_patch(int ni, const H2Args& h, hipStream_t st) {
 
 // Instantiated in conv_h2.hip (PRE) and conv_h2_raw.hip (a filter in KCRS[16]c[16]k).
 template <bool PRE, bool XY>
-hipError_t dispatch_h2(const ConvConfig& c, int ni, const H2Args& h, hipStream_t st) {
+hipError_t dispatch_h2(const ConvConfig& c, int ni, bool small, const H2Args& h, hipStream_t st) {
     switch (c.fk * 8 + c.fp) {
-        case 2 * 8 + 2: return dispatch_h2_patch<2, 2, PRE, XY>(ni, h, st);
-        case 2 * 8 + 4: return dispatch_h2_patch<4, 2, PRE, XY>(ni, h, st);
-        case 4 * 8 + 2: return dispatch_h2_patch<2, 4, PRE, XY>(ni, h, st);
-        case 4 * 8 + 4: return dispatch_h2_patch<4, 4, PRE, XY>(ni, h, st);
+        case 2 * 8 + 2: return dispatch_h2_patch<2, 2, PRE, XY>(ni, small, h, st);
+        case 2 * 8 + 4: return dispatch_h2_patch<4, 2, PRE, XY>(ni, small, h, st);
+        case 4 * 8 + 2: return dispatch_h2_patch<2, 4, PRE, XY>(ni, small, h, st);
+        case 4 * 8 + 4: return dispatch_h2_patch<4, 4, PRE, XY>(ni, small, h, st);
         default: return hipErrorInvalidValue;
     }
 }

@@ -5,7 +5,7 @@
 namespace neo {
 namespace conv_detail {
 
-template hipError_t dispatch_h2<true, false>(const ConvConfig&, int, const H2Args&, hipStream_t);
+template hipError_t dispatch_h2<true, false>(const ConvConfig&, int, bool, const H2Args&, hipStream_t);
 
 namespace {
 

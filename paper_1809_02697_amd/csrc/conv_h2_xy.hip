@@ -5,7 +5,7 @@
 namespace neo {
 namespace conv_detail {
 
-template hipError_t dispatch_h2<true, true>(const ConvConfig&, int, const H2Args&, hipStream_t);
+template hipError_t dispatch_h2<true, true>(const ConvConfig&, int, bool, const H2Args&, hipStream_t);
 
 }  // namespace conv_detail
 }  // namespace neo

@@ -54,6 +54,11 @@ CASES = [
     (96, 200, 3, 3, 1, 1, 40, 40, 1, "relu"),       # blocks of one image
     (5, 20, 3, 3, 1, 0, 5, 5, 1, "none"),           # fewer pixels than one instruction's
     (32, 48, 1, 2, 2, 0, 20, 24, 2, "relu"),        # stride above the window
+    (3, 64, 7, 7, 2, 3, 45, 50, 2, "relu"),         # stems: a window of whole column groups and a part of one,
+    (1, 20, 3, 3, 1, 1, 12, 9, 3, "res"),           # one channel, rows of several images,
+    (4, 40, 5, 5, 2, 2, 21, 11, 2, "relu"),         # four,
+    (3, 33, 1, 1, 1, 0, 30, 31, 1, "none"),         # pointwise,
+    (2, 16, 5, 1, 2, 1, 70, 33, 1, "relu"),         # stride above the window's width
 ]
 
 
@@ -80,7 +85,7 @@ def test_every_tile_and_split(neo, e, monkeypatch):
         err = assert_close(y, ref, cfg)
         assert err <= 1.5 * max(tile, 2e-8), (err, tile)
         np.testing.assert_array_equal(run(neo, c), y)
-        for xb, yb in [(32, 16), (16, 64)]:
+        for xb, yb in [(32, 16), (16, 64)] + ([(1, 16), (4, 32)] if c.C <= 4 else []):
             np.testing.assert_array_equal(run(neo, c, xb, yb), y, err_msg=f"{cfg} {xb}/{yb}")
 
 
@@ -106,7 +111,7 @@ def test_plan_with_converted_filters(neo, e, tmp_path):
         print(f"\n[h2 plan] {e} {cfg}", flush=True)
         p = neo.Plan(g, flags=neo.PLAN_HIPGRAPH)
         conv = [s for s in p.describe()["steps"] if s["kind"] == "conv"][0]["conv"]
-        if C > 4:
+        if C > 4 or not cfg.endswith(" 2 0"):
             assert conv["waves"] == 0 and conv["tuned"]
         x = dev(g.x)
         y = host(p.run(x))
@@ -128,15 +133,18 @@ def _both(neo, c, monkeypatch, cfg, **kw):
 def test_infinities_and_nans(neo, cfg, monkeypatch):
     """Infinite and NaN inputs and weights, and the largest float: the same
     non-finite outputs as the tile kernel, the finite ones within tolerance."""
-    c = wl.conv_case(40, 48, 3, 3, 1, 1, 12, 12, N=2, epilogue="none", with_bn=False)
-    for kind in range(3):
+    for kind in range(6):
+        C = 3 if kind > 2 else 40
+        if C == 3 and "2,0" in cfg:
+            break
+        c = wl.conv_case(C, 48, 3, 3, 1, 1, 12, 12, N=2, epilogue="none", with_bn=False)
         x, w = c.x.copy(), c.w.copy()
-        if kind == 0:
-            x[0, 3, 4, 5], x[1, 39, 0, 0], x[1, 20, 11, 11] = np.inf, np.nan, -np.inf
-        elif kind == 1:
-            w[7, 3, 1, 1], w[40, 11, 0, 2] = np.inf, np.nan
+        if kind % 3 == 0:
+            x[0, 2, 4, 5], x[1, C - 1, 0, 0], x[1, 1, 11, 11] = np.inf, np.nan, -np.inf
+        elif kind % 3 == 1:
+            w[7, 2, 1, 1], w[40, 1, 0, 2] = np.inf, np.nan
         else:
-            x[0, 5, 6, 6] = np.finfo(np.float32).max
+            x[0, 1, 6, 6] = np.finfo(np.float32).max
         print(f"\n[h2 non-finite] {cfg} {kind}", flush=True)
         t, y = _both(neo, c, monkeypatch, cfg, x=x, w=w)
         np.testing.assert_array_equal(np.isnan(y), np.isnan(t))
@@ -179,9 +187,9 @@ def test_range_of_values(neo, cfg, monkeypatch):
 
 
 def test_refused_where_it_does_not_apply(neo, tmp_path):
-    """Stems (at most four channels) keep the tile kernel whatever the results
-    file says, and so does a window whose patch exceeds the workgroup's."""
-    for C, R, H in ((3, 3, 12), (8, 25, 64)):
+    """A window whose patch exceeds the workgroup's keeps the tile kernel
+    whatever the results file says."""
+    for C, R, H in ((8, 25, 64),):
         neo.tune_db_clear()
         g = wl.Graph(name="one", input_shape=(1, C, H, H))
         c = wl.conv_case(C, 16, R, R, 1, 0, H, H)
