@@ -188,7 +188,9 @@ namespace {
 // share its matrix and vector units, where a step takes 96 fp + 181 cycles and
 // a float4 264.  The constants are a fit to 2,174 measured launches (220
 // shapes of 1x1 to 7x7 kernels at batch 1 to 32, every tile, splits 1 to 8):
-// mean deviation 11 %.
+// mean deviation 11 %.  (Fitted before the LDS reads moved into the matrix
+// instructions' shadow, which took up to 9 % off launches that fill the chip and
+// added 3 % to some others; not fitted again.)
 double h2_time_us(const ConvShape& s, const ConvConfig& c) {
     H2Geometry g;
     if (!conv_h2_config_valid(s, c) || !h2_geometry(s, h2_pixels(c), &g)) return 1e30;

@@ -38,7 +38,7 @@
 //     (i, g) of the instruction's B operand reads the 16 bytes of half g at
 //     its pixel.
 //   - Filter: straight from memory into the instruction's lane order, no wave
-//     reading what another one does; a ring of kH2Ring steps in flight.  Plans
+//     reading what another one does; a ring of three or four steps in flight.  Plans
 //     keep the filter as converted terms in that order (h2_split_filter), a
 //     linear stream of 2 KB per step and 32 channels; a filter in float32
 //     KCRS[16]c[16]k is converted as it is used.
@@ -61,7 +61,8 @@ typedef float v16f __attribute__((ext_vector_type(16)));
 typedef int v4i __attribute__((ext_vector_type(4)));
 
 constexpr int kH2Waves = 4;
-constexpr int kH2Ring = 4;
+// Filter steps in flight: as many as the registers hold.
+constexpr int h2_ring(int np) { return np == 4 ? 3 : 4; }
 
 // Channel blocks per chunk of a pointwise layer, by its patch pixels / 64 (up
 // to eight float4 per thread in flight).
@@ -297,7 +298,7 @@ __device__ inline void h2_again(const H2Args& h, const H2Tile& t, int kb, int p0
 // small-channel path.
 template <int NP, int WK, int NI, int UC, bool PRE, bool XY, bool SMALL>
 __global__ __launch_bounds__(64 * kH2Waves, 2) void conv2d_h2(H2Args h) {
-    constexpr int WP = kH2Waves / WK;
+    constexpr int WP = kH2Waves / WK, kRing = h2_ring(NP);
     // v8h (small-channel path: v4h) of a plane; the 4 keep the halves' 8-byte
     // writes in different banks
     constexpr int kPlane = (SMALL ? 256 : 64) * NI + 4;
@@ -309,6 +310,9 @@ __global__ __launch_bounds__(64 * kH2Waves, 2) void conv2d_h2(H2Args h) {
     __shared__ int where[2][NP * WP * 32];
     __shared__ __align__(16) float lbias[WK * 32];
     __shared__ int lexp[WK * 32];
+    // the threads' patch offsets, read again for every chunk where the registers are full
+    constexpr bool kOffLds = NP == 4 && !SMALL;
+    __shared__ unsigned loff[kOffLds ? NI : 1][kOffLds ? 64 * kH2Waves : 1];
     const ConvArgs& a = h.a;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -356,15 +360,27 @@ __global__ __launch_bounds__(64 * kH2Waves, 2) void conv2d_h2(H2Args h) {
     unsigned xoff[NI];
 #pragma unroll
     for (int j = 0; j < NI; ++j) xoff[j] = tile.input<XY>(h, xp + (SMALL ? 256 : 64) * j) + (SMALL ? 0 : 16 * xq);
+    if constexpr (kOffLds) {
+#pragma unroll
+        for (int j = 0; j < NI; ++j) loff[j][threadIdx.x] = xoff[j];
+    }
     const int dx = __builtin_amdgcn_readfirstlane(a.H * a.W * 64);
-    auto load_x = [&](v4f (&v)[UC][NI], int cb0) {
+    auto load_x = [&](v4f (&v)[UC][NI], int cb0) __attribute__((always_inline)) {
+        unsigned o[NI];
+#pragma unroll
+        for (int j = 0; j < NI; ++j) {
+            if constexpr (kOffLds)
+                o[j] = loff[j][threadIdx.x];
+            else
+                o[j] = xoff[j];
+        }
 #pragma unroll
         for (int c = 0; c < UC; ++c) {
             // (a block past the split's last is never multiplied)
             const int cb = min(cb0 + c, c_hi - 1);
             const int so = __builtin_amdgcn_readfirstlane(XY ? xgroup(a, cb) : cb * dx);
 #pragma unroll
-            for (int j = 0; j < NI; ++j) v[c][j] = SMALL ? h2_small_x<XY>(a, xr, xoff[j]) : ld4(xr, xoff[j], so, 0);
+            for (int j = 0; j < NI; ++j) v[c][j] = SMALL ? h2_small_x<XY>(a, xr, o[j]) : ld4(xr, o[j], so, 0);
         }
     };
     auto max_x = [&](const v4f (&v)[UC][NI], float m) {
@@ -389,7 +405,7 @@ __global__ __launch_bounds__(64 * kH2Waves, 2) void conv2d_h2(H2Args h) {
     const int w_end = __builtin_amdgcn_readfirstlane((f_hi - 1) * kStep);
     int w_at = __builtin_amdgcn_readfirstlane(f_lo * kStep);  // the next step's block (stays at the last one)
     int w_r = 0, w_u = 0;  // small-channel float32 filter: the next step's row and column group
-    auto load_w = [&](v4f (&v)[2], int so) {
+    auto load_w = [&](v4f (&v)[2], int so) __attribute__((always_inline)) {
         if constexpr (PRE) {
             v[0] = ld4(wr, woff, so, 0);
             v[1] = ld4(wr, woff, so, 1024);
@@ -406,7 +422,7 @@ __global__ __launch_bounds__(64 * kH2Waves, 2) void conv2d_h2(H2Args h) {
             for (int t = 0; t < 8; ++t) v[t / 4][t % 4] = ld1(wr, woff, so, t * 64);
         }
     };
-    auto next_w = [&](v4f (&v)[2]) {
+    auto next_w = [&](v4f (&v)[2]) __attribute__((always_inline)) {
         if constexpr (SMALL && !PRE) {
             load_w(v, __builtin_amdgcn_readfirstlane((w_r * a.S + 4 * w_u) * 1024));
             const bool row = w_u + 1 == a.U, last = row && w_r + 1 == a.R;
@@ -418,7 +434,7 @@ __global__ __launch_bounds__(64 * kH2Waves, 2) void conv2d_h2(H2Args h) {
         }
     };
 
-    v4f wv[kH2Ring][2], xv[UC][NI];
+    v4f wv[kRing][2], xv[UC][NI];
     // ---- scales
     int ew = 0, ex;
     {
@@ -430,13 +446,13 @@ __global__ __launch_bounds__(64 * kH2Waves, 2) void conv2d_h2(H2Args h) {
         }
         load_x(xv, c_lo);
 #pragma unroll
-        for (int d = 0; d < kH2Ring; ++d) next_w(wv[d]);
+        for (int d = 0; d < kRing; ++d) next_w(wv[d]);
         const float mx = h2_wave_max(max_x(xv, h2_max(mid, 0.f)));
         if (lane == 0) top[wave] = __float_as_uint(mx);
         if constexpr (!PRE) {
             float mw = h2_max(wmid[0], h2_max(wmid[1], 0.f));
 #pragma unroll
-            for (int d = 0; d < kH2Ring; ++d) mw = h2_max(wv[d][0], h2_max(wv[d][1], mw));
+            for (int d = 0; d < kRing; ++d) mw = h2_max(wv[d][0], h2_max(wv[d][1], mw));
             ew = __builtin_amdgcn_readfirstlane(h2_exponent(__float_as_uint(h2_wave_max(mw))));
         }
         __syncthreads();
@@ -447,21 +463,22 @@ __global__ __launch_bounds__(64 * kH2Waves, 2) void conv2d_h2(H2Args h) {
     }
     const float sclx = ldexpf(1.f, ex), sclx2 = sclx * 2048.f;
     const float sclw = ldexpf(1.f, ew), sclw2 = sclw * 2048.f;
-    auto stage = [&](int buf) {
+    auto stage_one = [&](int buf, int c, int j) __attribute__((always_inline)) {
+        v4h t[2];
+        h2_terms(xv[c][j], sclx, sclx2, t[0], t[1]);
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            if constexpr (SMALL)
+                reinterpret_cast<v4h*>(&xl[0][0][e][0][0])[xp + 256 * j] = t[e];
+            else
+                reinterpret_cast<v4h*>(&xl[buf][c][e][xq >> 1][xp + 64 * j])[xq & 1] = t[e];
+        }
+    };
+    auto stage = [&](int buf) __attribute__((always_inline)) {
 #pragma unroll
         for (int c = 0; c < UC; ++c)
 #pragma unroll
-            for (int j = 0; j < NI; ++j) {
-                v4h t[2];
-                h2_terms(xv[c][j], sclx, sclx2, t[0], t[1]);
-#pragma unroll
-                for (int e = 0; e < 2; ++e) {
-                    if constexpr (SMALL)
-                        reinterpret_cast<v4h*>(&xl[0][0][e][0][0])[xp + 256 * j] = t[e];
-                    else
-                        reinterpret_cast<v4h*>(&xl[buf][c][e][xq >> 1][xp + 64 * j])[xq & 1] = t[e];
-                }
-            }
+            for (int j = 0; j < NI; ++j) stage_one(buf, c, j);
     };
 
     v16f acc[NP], accl[NP];
@@ -483,18 +500,14 @@ __global__ __launch_bounds__(64 * kH2Waves, 2) void conv2d_h2(H2Args h) {
         }
     }
 
-    // Term h of the next step's input is read from LDS ahead of this step's
-    // matrix instructions, and term l of this one's at its start, under the
-    // instructions that need only h: without that every step waits for its
-    // own reads.
-    v8h xh[2][NP], xlo[NP];
+    v8h xh[NP], xlo[NP];
     if (threadIdx.x < WK * 32) {
         lbias[threadIdx.x] = my_bias;
         lexp[threadIdx.x] = my_exp;
     }
     const v8h* const x0 = &xl[0][0][0][0][0];
     constexpr int kBlock = 4 * kPlane, kBuffer = UC * kBlock;
-    auto read = [&](int i, int e) {  // term e at index i
+    auto read = [&](int i, int e) __attribute__((always_inline)) {  // term e at index i
         if constexpr (SMALL) {
             const v4h* q = reinterpret_cast<const v4h*>(x0) + i + e * kPlane;
             return h2_join(q[0], q[1]);
@@ -506,64 +519,118 @@ __global__ __launch_bounds__(64 * kH2Waves, 2) void conv2d_h2(H2Args h) {
     if constexpr (!SMALL) load_x(xv, c_lo + UC);
     __syncthreads();
 #pragma unroll
-    for (int p = 0; p < NP; ++p) xh[0][p] = read(at[p], 0);
-    // off: this step's input from the lane's first (a chunk of one block walks
-    // the kernel entries, a pointwise chunk its blocks); left: steps of the chunk
+    for (int p = 0; p < NP; ++p) {
+        xh[p] = read(at[p], 0);
+        xlo[p] = read(at[p], 1);
+    }
+    // off: the step's input from the lane's first (a chunk of one block walks
+    // the kernel entries, a pointwise chunk its blocks); left: steps of the
+    // chunk from this one on, at least two in a whole chunk
     const int per_chunk = UC > 1 ? UC : __builtin_amdgcn_readfirstlane(per_block);
     const int columns = SMALL ? a.U : a.S;  // steps of a kernel row
     constexpr int kColumn = SMALL ? 4 : 1;
     const int row_skip = __builtin_amdgcn_readfirstlane(h.PW - kColumn * columns);
     int buf = 0, off = 0, s = columns, left = per_chunk, cb = c_lo;
-    for (int f0 = f_lo; f0 < f_hi; f0 += kH2Ring) {
+    auto advance = [&]() __attribute__((always_inline)) {
+        if constexpr (UC > 1) {
+            off += kBlock;
+        } else {
+            const bool row = --s == 0;
+            off += row ? row_skip + kColumn : kColumn;
+            s = row ? columns : s;
+        }
+        const bool end = --left == 0;  // (s is `columns` again)
+        if constexpr (!SMALL) {
+            buf ^= end ? 1 : 0;
+            cb += end ? UC : 0;
+        }
+        off = end ? (buf ? kBuffer : 0) : off;
+        left = end ? per_chunk : left;
+    };
+    // A step's 3 NP matrix instructions run back to back only if nothing that
+    // they read is still on its way, so everything else stands between them, in
+    // their shadow, held there by scheduling fences (left alone the scheduler
+    // puts the LDS reads right before their use, and a wait in front of every
+    // second instruction):
+    //   - an operand of the next step's input is read from LDS as soon as this
+    //     step's instructions have taken the last from its registers;
+    //   - a float32 filter's next step is converted, a pair of elements a time.
+    // A chunk's last step but one ends with the next chunk's input converted and
+    // written to the other buffer, and the barrier; the last step then reads
+    // ahead into the new chunk.  (Every wave's last reads of the other buffer
+    // lie before the barrier one chunk earlier.)
+    // Before and after: 256 -> 256 3x3 at 56x56 batch 8 118 -> 107 us (277
+    // TFLOP/s), 64 -> 64 at 56x56 batch 32 39.0 -> 35.4 us, ResNet-50 batch 32
+    // 1.76 -> 1.67 ms (1.79 -> 1.72 on another card); a float32 filter with one or two workgroups on a CU (128
+    // -> 128 at 28x28 batch 32) is bound by the filter's loads, 38.3 -> 39.4 us.
+    // The conversions in a branch of each slot, between the instructions, took
+    // 42.4 us there: a branch taken costs more than the shadow holds.
+    v8h w[2];  // the step's filter terms
+    auto convert_w = [&](const v4f (&v)[2], v8h (&o)[2], int pair) __attribute__((always_inline)) {
+        if constexpr (!PRE) {
 #pragma unroll
-        for (int d = 0; d < kH2Ring; ++d) {
-            if (f0 + d >= f_hi) break;
-#pragma unroll
-            for (int p = 0; p < NP; ++p) xlo[p] = read(at[p] + off, 1);
-            if constexpr (UC > 1) {
-                off += kBlock;
-            } else {
-                const bool row = --s == 0;
-                off += row ? row_skip + kColumn : kColumn;
-                s = row ? columns : s;
-            }
-            const bool swap = --left == 0;
-            off = swap ? 0 : off;
-            // (the chunk's last step reads its first again, in range and unused)
-#pragma unroll
-            for (int p = 0; p < NP; ++p) xh[(d + 1) & 1][p] = read(at[p] + off, 0);
-            v8h w[2];
-            if constexpr (PRE) {
-                w[0] = __builtin_bit_cast(v8h, wv[d][0]);
-                w[1] = __builtin_bit_cast(v8h, wv[d][1]);
-            } else {
-                v4h t[2][2];
-                h2_terms(wv[d][0], sclw, sclw2, t[0][0], t[1][0]);
-                h2_terms(wv[d][1], sclw, sclw2, t[0][1], t[1][1]);
-                w[0] = h2_join(t[0][0], t[0][1]);
-                w[1] = h2_join(t[1][0], t[1][1]);
-            }
-#pragma unroll
-            for (int p = 0; p < NP; ++p) {
-                acc[p] = __builtin_amdgcn_mfma_f32_32x32x16_f16(w[0], xh[d & 1][p], acc[p], 0, 0, 0);
-                accl[p] = __builtin_amdgcn_mfma_f32_32x32x16_f16(w[1], xh[d & 1][p], accl[p], 0, 0, 0);
-            }
-#pragma unroll
-            for (int p = 0; p < NP; ++p)
-                accl[p] = __builtin_amdgcn_mfma_f32_32x32x16_f16(w[0], xlo[p], accl[p], 0, 0, 0);
-            next_w(wv[d]);
-            if (!SMALL && swap && f0 + d + 1 < f_hi) {
-                left = per_chunk;
-                cb += UC;
-                buf ^= 1;
-                stage(buf);
-                load_x(xv, cb + UC);
-                __syncthreads();
-                off = buf ? kBuffer : 0;
-#pragma unroll
-                for (int p = 0; p < NP; ++p) xh[(d + 1) & 1][p] = read(at[p] + off, 0);
+            for (int e = 2 * pair; e < 2 * pair + 2; ++e) {
+                const float f = v[e / 4][e % 4];
+                o[0][e] = (_Float16)__builtin_fmaf(f, sclw, 0.f);
+                o[1][e] = (_Float16)__builtin_fmaf((float)o[0][e], -2048.f, f * sclw2);
             }
         }
+    };
+    auto step = [&](v4f (&wd)[2], const v4f (&wnext)[2]) __attribute__((always_inline)) {
+        const bool stage_next = !SMALL && left == 2 && cb + UC < c_hi;
+        if constexpr (PRE) {
+            w[0] = __builtin_bit_cast(v8h, wd[0]);
+            w[1] = __builtin_bit_cast(v8h, wd[1]);
+        }
+        v8h wn[2];
+        const int other = buf ^ 1;
+        advance();
+        __builtin_amdgcn_sched_barrier(0);
+        auto between = [&](int slot) __attribute__((always_inline)) {  // of 2 NP
+            if (slot < 4) convert_w(wnext, wn, slot);
+        };
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+            acc[p] = __builtin_amdgcn_mfma_f32_32x32x16_f16(w[0], xh[p], acc[p], 0, 0, 0);
+            accl[p] = __builtin_amdgcn_mfma_f32_32x32x16_f16(w[1], xh[p], accl[p], 0, 0, 0);
+            xh[p] = read(at[p] + off, 0);
+            between(p);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+            accl[p] = __builtin_amdgcn_mfma_f32_32x32x16_f16(w[0], xlo[p], accl[p], 0, 0, 0);
+            xlo[p] = read(at[p] + off, 1);
+            between(NP + p);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        next_w(wd);
+        if constexpr (!PRE) {
+            w[0] = wn[0];
+            w[1] = wn[1];
+        }
+        if (stage_next) {
+            stage(other);
+            load_x(xv, cb + 2 * UC);
+            __syncthreads();
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    if constexpr (!PRE) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) convert_w(wv[0], w, q);
+    }
+    // (whole turns of the ring, then what remains: with an exit inside the turn
+    // the waits for loads at the loop's head would count the ways that skip later loads)
+    int f = f_lo;
+    for (; f + kRing <= f_hi; f += kRing) {
+#pragma unroll
+        for (int d = 0; d < kRing; ++d) step(wv[d], wv[(d + 1) % kRing]);
+    }
+#pragma unroll
+    for (int d = 0; d + 1 < kRing; ++d) {
+        if (f + d >= f_hi) break;
+        step(wv[d], wv[d + 1]);
     }
 
     // join the sums; a non-finite one means a value out of range
