@@ -561,10 +561,10 @@ __global__ __launch_bounds__(64 * kH2Waves, 2) void conv2d_h2(H2Args h) {
     // lie before the barrier one chunk earlier.)
     // Before and after: 256 -> 256 3x3 at 56x56 batch 8 118 -> 107 us (277
     // TFLOP/s), 64 -> 64 at 56x56 batch 32 39.0 -> 35.4 us, ResNet-50 batch 32
-    // 1.76 -> 1.67 ms (1.79 -> 1.72 on another card); a float32 filter with one or two workgroups on a CU (128
-    // -> 128 at 28x28 batch 32) is bound by the filter's loads, 38.3 -> 39.4 us.
-    // The conversions in a branch of each slot, between the instructions, took
-    // 42.4 us there: a branch taken costs more than the shadow holds.
+    // 1.76 -> 1.67 ms (1.79 -> 1.72 on another card); a float32 filter with one
+    // or two workgroups on a CU (128 -> 128 at 28x28 batch 32) 38.3 -> 39.4 us.
+    // The next chunk's conversions in a branch of each slot, between the
+    // instructions, took 42.4 us there: a branch costs more than the shadow holds.
     v8h w[2];  // the step's filter terms
     auto convert_w = [&](const v4f (&v)[2], v8h (&o)[2], int pair) __attribute__((always_inline)) {
         if constexpr (!PRE) {
