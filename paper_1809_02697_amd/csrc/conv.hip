@@ -360,6 +360,7 @@ hipError_t launch_conv2d(const ConvShape& s, const ConvConfig& c, const float* x
         a.kfirst = g.tiles * a.div_nkb.d >= kKFirstMinWgs;
         h.w32 = w;
         h.w32_bytes = a.w_bytes;
+        h.K = s.K;
         h.wexp = nullptr;
         if (wmfma) {
             const long blocks = (long)cdiv(a.KB, 2) * h2_filter_steps(s);

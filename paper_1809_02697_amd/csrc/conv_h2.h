@@ -6,24 +6,31 @@
 //   s v = h + 2^-11 l + e,  h = fp16(s v),  l = fp16(2^11 (s v - h)):
 // 11 bits, then 11 more of the remainder, whose sign is a twelfth; the
 // remainder has at most 12 bits and a sign, so |e| is at most one unit of v's
-// last place and zero for three values in four.  A product is h h' + 2^-11
-// (h l' + l h'); the dropped l l' lies below 2^-22 of it, with either sign.
+// last place and zero for three values in four.  (Single precision from fp16
+// products of two terms, the second scaled by 2^11: Markidis et al. 2018;
+// Ootomo and Yokota 2022.)  A product is h h' + 2^-11 (h l' + l h'); the
+// dropped l l' lies below 2^-22 of it, with either sign.
 // The two sums are kept in float32 accumulators of their own (so l needs no
 // further bits of fp16's range) and joined at the end.  Three 32x32x16 fp16
 // instructions (96 cycles) replace eight 32x32x2 float32 ones (512 cycles),
-// and the sum is rounded once per 16 products instead of once per 2: against
-// a float64 reference the result is closer than the float32 kernel's (the
-// measured errors stand with the choice of the kernel, conv.hip).
+// and the sum is rounded once per 16 products instead of once per 2.
 //
-// Range.  Filters are scaled per output channel, inputs per workgroup (and
-// filters that arrive in float32 per wave): the scale puts the largest
-// magnitude -- of the channel, or of the sampled operands: the first chunk of
-// the reduction and one in its middle -- at 2^10 .. 2^11.  Values up to 2^5
-// times that are exact as above; so are values down to 2^-22 of it, and
-// smaller ones keep an absolute error of 2^-46 of it.  A value beyond the
-// range (or an infinity or NaN) becomes infinite in h and makes every sum it
-// enters non-finite: a wave that finds such a sum computes its tile again on
-// float32 MFMA from memory.
+// Range.  Filters are scaled per output channel, inputs per workgroup.  The
+// scale puts the largest magnitude of a converted channel at 2^14 .. 2^15; of
+// the input, and of a float32 filter's channels, it puts the largest of a
+// sample at 2^10 .. 2^11: the input's first chunk and a float4 per thread in
+// the middle of the reduction, the filter's first steps and its middle one.
+//   - A value beyond the range (or an infinity or NaN) becomes infinite in h
+//     and makes every sum it enters non-finite.
+//   - A small value, below 2^-12 once scaled, keeps an error of up to 2^-36, which
+//     is no longer a part of itself.  Small values are counted as they are
+//     converted; at the end of the reduction the count bounds the error that
+//     they can have left in a sum.
+// A wave that finds a sum of its tile not finite, or not 2^20 times above that
+// bound, computes the tile again on float32 MFMA from memory.  So every sum
+// has a float32 sum's error for its own terms, whatever lies beside them.
+// In a map of ordinary values a tile in fifty meets a small value, and one in
+// millions of its sums lies as low as what a few of them leave.
 //
 // Tile.  A workgroup of four waves, WK along the output channels, computes
 // 32 WK channels x 32 NP (4 / WK) pixels; a wave 32 channels x 32 NP pixels.
@@ -55,6 +62,8 @@
 namespace neo {
 namespace conv_detail {
 
+typedef float v2f __attribute__((ext_vector_type(2)));
+typedef _Float16 v2h __attribute__((ext_vector_type(2)));
 typedef _Float16 v4h __attribute__((ext_vector_type(4)));
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 typedef float v16f __attribute__((ext_vector_type(16)));
@@ -73,8 +82,9 @@ enum { kH2Point = 0, kH2Rows = 1, kH2Block = 2 };
 struct H2Args {
     ConvArgs a;
     const float* w32;  // the float32 filter: KCRS[16]c[16]k, or with a converted filter the kernel order
-    const int* wexp;   // per output channel: the exponent of the converted filter's scale
+    const int* wexp;   // per output channel of the converted filter: h2_channel()
     int w32_bytes;
+    int K;             // output channels (without the last block's padding)
     // kH2Point: consecutive pixels of a 1x1 layer, the patch is the pixels'
     // own inputs.  kH2Rows: consecutive pixels (n, oh, ow); the patch is the
     // input rows their windows touch, whole, image by image.  kH2Block: a
@@ -88,13 +98,23 @@ struct H2Args {
     int chunks;         // chunks of the reduction
 };
 
-// The two terms of s v, s2 = 2^11 s.
-__device__ inline void h2_terms(const v4f& x, float s, float s2, v4h& h, v4h& l) {
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        h[j] = (_Float16)__builtin_fmaf(x[j], s, 0.f);
-        l[j] = (_Float16)__builtin_fmaf((float)h[j], -2048.f, x[j] * s2);
-    }
+// The two terms of a pair of values scaled by s, s2 = 2^11 s: six instructions.
+// (The empty statements keep the pair in one register: without them the
+// compiler converts a value twice, or takes an instruction more for the second term.)
+__device__ inline void h2_pair(float x0, float x1, float s2, v2h& h, v2h& l) {
+    const float u0 = x0 * s2, u1 = x1 * s2;
+    h = v2h{(_Float16)__builtin_fmaf(u0, 1.f / 2048.f, 0.f), (_Float16)__builtin_fmaf(u1, 1.f / 2048.f, 0.f)};
+    asm("" : "+v"(h));
+    _Float16 l0 = (_Float16)__builtin_fmaf((float)h[0], -2048.f, u0);
+    asm("" : "+v"(l0));
+    l = v2h{l0, (_Float16)__builtin_fmaf((float)h[1], -2048.f, u1)};
+}
+__device__ inline void h2_terms(const v4f& x, float s2, v4h& h, v4h& l) {
+    v2h a[2], b[2];
+    h2_pair(x[0], x[1], s2, a[0], b[0]);
+    h2_pair(x[2], x[3], s2, a[1], b[1]);
+    h = __builtin_shufflevector(a[0], a[1], 0, 1, 2, 3);
+    l = __builtin_shufflevector(b[0], b[1], 0, 1, 2, 3);
 }
 __device__ inline v8h h2_join(const v4h& a, const v4h& b) { return __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7); }
 
@@ -103,19 +123,51 @@ __device__ inline float h2_max(const v4f& x, float m) {
     for (int j = 0; j < 4; ++j) m = fmaxf(m, fabsf(x[j]));
     return m;
 }
+// min(m, |a|, |b|) in one instruction (fminf makes its operands canonical first).
+__device__ inline float h2_min3(float m, float a, float b) {
+    asm("v_min3_f32 %0, %0, |%1|, |%2|" : "+v"(m) : "v"(a), "v"(b));
+    return m;
+}
 __device__ inline float h2_wave_max(float m) {
 #pragma unroll
     for (int d = 32; d > 0; d >>= 1) m = fmaxf(m, __shfl_xor(m, d, 64));
     return m;
 }
 
-// The exponent n of the scale 2^n that takes magnitude m (its float bits) to
-// 2^10 .. 2^11; 0 for no magnitude, an infinity or NaN.
-__device__ inline int h2_exponent(unsigned m) {
+// The magnitudes that the scales take the largest one to, 2^top .. 2^(top + 1):
+// the largest of a sample (with room above), of a whole filter channel.
+constexpr int kH2TopSample = 10, kH2TopAll = 14;
+
+// The exponent n of the scale 2^n that takes magnitude m (its float bits) there;
+// 0 for no magnitude, an infinity or NaN.
+__device__ inline int h2_exponent(unsigned m, int top) {
     const int e = (int)(m >> 23);
     if (m == 0 || e == 255) return 0;
-    return min(137 - e, 110);
+    return min(127 + top - e, 110);
 }
+
+// v is a small value if h2_key(v) < h2_key(h2_small(n)), n the exponent of its
+// scale (a zero's key is the largest).
+__device__ inline unsigned h2_key(float v) { return (__float_as_uint(v) << 1) - 1u; }
+__device__ inline float h2_small(int n) { return ldexpf(1.f, -12 - n); }
+
+// min(m, the values' keys), two keys an instruction.  Of a pair, a zero beside a
+// negative value may read 0 or 1 below its key: small, as zeros are not.
+__device__ inline unsigned h2_low(const v4f& x, unsigned m) {
+    typedef unsigned v2u __attribute__((ext_vector_type(2)));
+#pragma unroll
+    for (int j = 0; j < 4; j += 2) {
+        const v2f p = {x[j], x[j + 1]};
+        const v2u k = __builtin_bit_cast(v2u, (__builtin_bit_cast(unsigned long, p) << 1) + 0xfffffffeffffffffUL);
+        m = min(min(m, k[0]), k[1]);
+    }
+    return m;
+}
+
+// A filter channel's scale exponent and its number of small values (at most 65535).
+__device__ inline int h2_channel(int exponent, int small) { return exponent * 65536 + min(small, 65535); }
+__device__ inline int h2_channel_exponent(int c) { return c >> 16; }
+__device__ inline int h2_channel_small(int c) { return c & 65535; }
 
 // The geometry of one workgroup's tile: where its pixels and patch pixels lie.
 struct H2Tile {
@@ -296,14 +348,20 @@ __device__ inline void h2_again(const H2Args& h, const H2Tile& t, int kb, int p0
 
 // NI: patch pixels per 64 (the patch has at most 64 NI pixels), per 256 on the
 // small-channel path.
+// Workgroups per CU that the registers are kept for: three for two pixel blocks
+// a wave and a small patch.
+constexpr int h2_resident(int np, int items, bool pre, bool small) {
+    return np == 2 && (small || items <= (pre ? 5 : 3)) ? 3 : 2;
+}
+
 template <int NP, int WK, int NI, int UC, bool PRE, bool XY, bool SMALL>
-__global__ __launch_bounds__(64 * kH2Waves, 2) void conv2d_h2(H2Args h) {
+__global__ __launch_bounds__(64 * kH2Waves, h2_resident(NP, UC * NI, PRE, SMALL)) void conv2d_h2(H2Args h) {
     constexpr int WP = kH2Waves / WK, kRing = h2_ring(NP);
     // v8h (small-channel path: v4h) of a plane; the 4 keep the halves' 8-byte
     // writes in different banks
     constexpr int kPlane = (SMALL ? 256 : 64) * NI + 4;
     __shared__ v8h xl[SMALL ? 1 : 2][SMALL ? 1 : UC][2][SMALL ? 1 : 2][SMALL ? kPlane / 2 : kPlane];
-    __shared__ unsigned top[kH2Waves];
+    __shared__ unsigned top[kH2Waves], small[kH2Waves];
     // for the epilogue: image and position of the tile's pixels, its channels'
     // bias and scale exponents (loaded now: at the end each load would wait
     // for a full round trip to memory)
@@ -435,50 +493,77 @@ __global__ __launch_bounds__(64 * kH2Waves, 2) void conv2d_h2(H2Args h) {
     };
 
     v4f wv[kRing][2], xv[UC][NI];
-    // ---- scales
+    // ---- scales: the input's exponent, and a float32 filter's of the lane's channel
     int ew = 0, ex;
     {
-        v4f mid = v4f{0.f, 0.f, 0.f, 0.f}, wmid[2] = {mid, mid};
-        if constexpr (!SMALL) {
-            const int cm = (c_lo + c_hi) / 2;
-            mid = ld4(xr, xoff[NI / 2], __builtin_amdgcn_readfirstlane(XY ? xgroup(a, cm) : cm * dx), 0);
-            if constexpr (!PRE) load_w(wmid, __builtin_amdgcn_readfirstlane((f_lo + f_hi) / 2 * kStep));
+        constexpr int kMid = SMALL ? 0 : 1;  // further blocks of the sample
+        v4f mid[kMid + 1], wmid[2] = {v4f{0.f, 0.f, 0.f, 0.f}, v4f{0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+        for (int q = 0; q < kMid; ++q) {
+            const int cm = c_lo + (c_hi - c_lo) * (q + 1) / (kMid + 1);
+            mid[q] = ld4(xr, xoff[(NI - 1) / 2], __builtin_amdgcn_readfirstlane(XY ? xgroup(a, cm) : cm * dx), 0);
         }
+        if constexpr (!SMALL && !PRE) load_w(wmid, __builtin_amdgcn_readfirstlane((f_lo + f_hi) / 2 * kStep));
         load_x(xv, c_lo);
 #pragma unroll
         for (int d = 0; d < kRing; ++d) next_w(wv[d]);
-        const float mx = h2_wave_max(max_x(xv, h2_max(mid, 0.f)));
+        float mx = 0.f;
+#pragma unroll
+        for (int q = 0; q < kMid; ++q) mx = h2_max(mid[q], mx);
+        mx = h2_wave_max(max_x(xv, mx));
         if (lane == 0) top[wave] = __float_as_uint(mx);
         if constexpr (!PRE) {
             float mw = h2_max(wmid[0], h2_max(wmid[1], 0.f));
 #pragma unroll
             for (int d = 0; d < kRing; ++d) mw = h2_max(wv[d][0], h2_max(wv[d][1], mw));
-            ew = __builtin_amdgcn_readfirstlane(h2_exponent(__float_as_uint(h2_wave_max(mw))));
+            mw = fmaxf(mw, __shfl_xor(mw, 32, 64));
+            mw = mw < __builtin_inff() ? mw : 0.f;
+            // a channel whose sample is all zeros (or not finite) takes the largest of the wave's
+            if (__any(mw == 0.f)) {
+                const float wave_mw = h2_wave_max(mw);
+                mw = mw > 0.f ? mw : wave_mw;
+            }
+            ew = h2_exponent(__float_as_uint(mw), kH2TopSample);
         }
         __syncthreads();
         unsigned t = 0;
 #pragma unroll
         for (int w = 0; w < kH2Waves; ++w) t = max(t, top[w]);
-        ex = __builtin_amdgcn_readfirstlane(h2_exponent(t));
+        ex = __builtin_amdgcn_readfirstlane(h2_exponent(t, kH2TopSample));
     }
-    const float sclx = ldexpf(1.f, ex), sclx2 = sclx * 2048.f;
-    const float sclw = ldexpf(1.f, ew), sclw2 = sclw * 2048.f;
-    auto stage_one = [&](int buf, int c, int j) __attribute__((always_inline)) {
+    const float sclx2 = ldexpf(1.f, ex + 11), sclw2 = ldexpf(1.f, ew + 11);
+    const unsigned x_small = h2_key(h2_small(ex));
+    const float w_small = h2_small(ew);
+    // the wave's small input values; its small filter values (at most), and the
+    // lanes (channels) that hold them
+    int n_small = 0, nw_small = 0;
+    unsigned long w_seen = 0;
+    auto stage_one = [&](int at, int c, int j, unsigned& low) __attribute__((always_inline)) {  // at: the buffer's v8h
         v4h t[2];
-        h2_terms(xv[c][j], sclx, sclx2, t[0], t[1]);
+        h2_terms(xv[c][j], sclx2, t[0], t[1]);
+        low = h2_low(xv[c][j], low);
 #pragma unroll
         for (int e = 0; e < 2; ++e) {
             if constexpr (SMALL)
                 reinterpret_cast<v4h*>(&xl[0][0][e][0][0])[xp + 256 * j] = t[e];
             else
-                reinterpret_cast<v4h*>(&xl[buf][c][e][xq >> 1][xp + 64 * j])[xq & 1] = t[e];
+                reinterpret_cast<v4h*>(&xl[0][c][e][xq >> 1][xp + 64 * j] + at)[xq & 1] = t[e];
         }
     };
-    auto stage = [&](int buf) __attribute__((always_inline)) {
+    auto stage = [&](int at) __attribute__((always_inline)) {
+        unsigned low = ~0u;
 #pragma unroll
         for (int c = 0; c < UC; ++c)
 #pragma unroll
-            for (int j = 0; j < NI; ++j) stage_one(buf, c, j);
+            for (int j = 0; j < NI; ++j) stage_one(at, c, j, low);
+        if (__any(low < x_small)) {
+#pragma unroll
+            for (int c = 0; c < UC; ++c)
+#pragma unroll
+                for (int j = 0; j < NI; ++j)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) n_small += __popcll(__ballot(h2_key(xv[c][j][e]) < x_small));
+        }
     };
 
     v16f acc[NP], accl[NP];
@@ -503,7 +588,10 @@ __global__ __launch_bounds__(64 * kH2Waves, 2) void conv2d_h2(H2Args h) {
     v8h xh[NP], xlo[NP];
     if (threadIdx.x < WK * 32) {
         lbias[threadIdx.x] = my_bias;
-        lexp[threadIdx.x] = my_exp;
+        if constexpr (PRE) lexp[threadIdx.x] = my_exp;
+    }
+    if constexpr (!PRE) {
+        if (lane < 32) lexp[wk * 32 + lane] = h2_channel(ew, 0);
     }
     const v8h* const x0 = &xl[0][0][0][0][0];
     constexpr int kBlock = 4 * kPlane, kBuffer = UC * kBlock;
@@ -530,22 +618,21 @@ __global__ __launch_bounds__(64 * kH2Waves, 2) void conv2d_h2(H2Args h) {
     const int columns = SMALL ? a.U : a.S;  // steps of a kernel row
     constexpr int kColumn = SMALL ? 4 : 1;
     const int row_skip = __builtin_amdgcn_readfirstlane(h.PW - kColumn * columns);
-    int buf = 0, off = 0, s = columns, left = per_chunk, cb = c_lo;
+    // base: the other buffer; next: the next chunk to stage, once `left` is stage_at
+    int off = 0, s = columns, left = per_chunk, base = SMALL ? 0 : kBuffer, next = c_lo + UC;
+    int stage_at = next < c_hi ? 2 : 0;
     auto advance = [&]() __attribute__((always_inline)) {
         if constexpr (UC > 1) {
             off += kBlock;
         } else {
-            const bool row = --s == 0;
-            off += row ? row_skip + kColumn : kColumn;
-            s = row ? columns : s;
+            --s;
+            off += s == 0 ? row_skip + kColumn : kColumn;
+            s = s == 0 ? columns : s;
         }
-        const bool end = --left == 0;  // (s is `columns` again)
-        if constexpr (!SMALL) {
-            buf ^= end ? 1 : 0;
-            cb += end ? UC : 0;
-        }
-        off = end ? (buf ? kBuffer : 0) : off;
-        left = end ? per_chunk : left;
+        --left;
+        off = left == 0 ? base : off;  // (s is `columns` again)
+        if constexpr (!SMALL) base ^= left == 0 ? kBuffer : 0;
+        left = left == 0 ? per_chunk : left;
     };
     // A step's 3 NP matrix instructions run back to back only if nothing that
     // they read is still on its way, so everything else stands between them, in
@@ -554,7 +641,11 @@ __global__ __launch_bounds__(64 * kH2Waves, 2) void conv2d_h2(H2Args h) {
     // second instruction):
     //   - an operand of the next step's input is read from LDS as soon as this
     //     step's instructions have taken the last from its registers;
-    //   - a float32 filter's next step is converted, a pair of elements a time.
+    //   - a float32 filter's own step is looked through for small values.
+    // The filter's next step is converted behind them, where its loads have had
+    // a whole step more (between the instructions: the same for 128 -> 128 at
+    // 28x28, but spilt registers for large patches, 64 -> 64 at 56x56 75 us
+    // against 37).
     // A chunk's last step but one ends with the next chunk's input converted and
     // written to the other buffer, and the barrier; the last step then reads
     // ahead into the new chunk.  (Every wave's last reads of the other buffer
@@ -568,26 +659,37 @@ __global__ __launch_bounds__(64 * kH2Waves, 2) void conv2d_h2(H2Args h) {
     v8h w[2];  // the step's filter terms
     auto convert_w = [&](const v4f (&v)[2], v8h (&o)[2], int pair) __attribute__((always_inline)) {
         if constexpr (!PRE) {
+            v2h t[2];
+            h2_pair(v[pair / 2][2 * pair % 4], v[pair / 2][2 * pair % 4 + 1], sclw2, t[0], t[1]);
 #pragma unroll
-            for (int e = 2 * pair; e < 2 * pair + 2; ++e) {
-                const float f = v[e / 4][e % 4];
-                o[0][e] = (_Float16)__builtin_fmaf(f, sclw, 0.f);
-                o[1][e] = (_Float16)__builtin_fmaf((float)o[0][e], -2048.f, f * sclw2);
+            for (int e = 0; e < 2; ++e) {
+                o[e][2 * pair] = t[e][0];
+                o[e][2 * pair + 1] = t[e][1];
             }
         }
     };
     auto step = [&](v4f (&wd)[2], const v4f (&wnext)[2]) __attribute__((always_inline)) {
-        const bool stage_next = !SMALL && left == 2 && cb + UC < c_hi;
+        const bool stage_next = !SMALL && left == stage_at;
         if constexpr (PRE) {
             w[0] = __builtin_bit_cast(v8h, wd[0]);
             w[1] = __builtin_bit_cast(v8h, wd[1]);
         }
         v8h wn[2];
-        const int other = buf ^ 1;
+        // The lowest of the lane's filter magnitudes, one instruction for two; only a
+        // step with one below the limit, most often a zero, is looked at by keys
+        // (always by keys: 128 -> 128 at 28x28 batch 32 45 us against 39).  Stems have
+        // zeros in every step.
+        float low = __builtin_inff();
+        unsigned key = ~0u;
         advance();
         __builtin_amdgcn_sched_barrier(0);
         auto between = [&](int slot) __attribute__((always_inline)) {  // of 2 NP
-            if (slot < 4) convert_w(wnext, wn, slot);
+            if constexpr (!PRE) {  // (the step's own values: the next one's are still on their way)
+                if (slot < 4 && SMALL)
+                    key = min(min(key, h2_key(wd[slot / 2][2 * slot % 4])), h2_key(wd[slot / 2][2 * slot % 4 + 1]));
+                else if (slot < 4)
+                    low = h2_min3(low, wd[slot / 2][2 * slot % 4], wd[slot / 2][2 * slot % 4 + 1]);
+            }
         };
 #pragma unroll
         for (int p = 0; p < NP; ++p) {
@@ -604,14 +706,33 @@ __global__ __launch_bounds__(64 * kH2Waves, 2) void conv2d_h2(H2Args h) {
             between(NP + p);
             __builtin_amdgcn_sched_barrier(0);
         }
-        next_w(wd);
         if constexpr (!PRE) {
+            auto count = [&]() __attribute__((always_inline)) {
+                const unsigned long m = __ballot(key < h2_key(w_small));
+                w_seen |= m;
+                nw_small += 8 * __popcll(m);
+            };
+            if constexpr (SMALL) {
+                count();
+            } else if (__any(low < w_small)) {  // (a zero, or a small value)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) key = min(key, h2_key(wd[e / 4][e % 4]));
+                count();
+            }
+        }
+        next_w(wd);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (!PRE) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) convert_w(wnext, wn, q);
             w[0] = wn[0];
             w[1] = wn[1];
         }
         if (stage_next) {
-            stage(other);
-            load_x(xv, cb + 2 * UC);
+            stage(base);
+            next += UC;
+            stage_at = next < c_hi ? 2 : 0;
+            load_x(xv, next);
             __syncthreads();
         }
         __builtin_amdgcn_sched_barrier(0);
@@ -642,7 +763,32 @@ __global__ __launch_bounds__(64 * kH2Waves, 2) void conv2d_h2(H2Args h) {
             acc[p][v] = __builtin_fmaf(accl[p][v], 1.f / 2048.f, acc[p][v]);
             bad = __builtin_fmaf(acc[p][v], 0.f, bad);
         }
-    const bool again = __any(bad != bad);
+    bool again = __any(bad != bad);
+    if (lane == 0) small[wave] = n_small;
+    __syncthreads();
+    unsigned x_count = 0;
+#pragma unroll
+    for (int w = 0; w < kH2Waves; ++w) x_count += small[w];
+    x_count = __builtin_amdgcn_readfirstlane(x_count);
+    const unsigned w_low = PRE ? (unsigned)__ballot(h2_channel_small(lexp[wk * 32 + (lane & 31)]) != 0)
+                               : (unsigned)(w_seen | (w_seen >> 32));
+    if (x_count | w_low) {
+        // m small inputs leave a sum an error of at most m 2^-36 times the
+        // largest weight (2^15, 2^16 from a sample), m small weights one of m
+        // 2^-36 times the largest input (2^16); 2^20 of both:
+        const float x_lim = (float)x_count * (PRE ? 0.5f : 1.f);
+        bool few = false;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const int c = 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
+            const float m = PRE ? (float)h2_channel_small(lexp[wk * 32 + c]) : ((w_low >> c) & 1) ? (float)nw_small : 0.f;
+            const float lim = kb * 32 + c < h.K ? x_lim + m : 0.f;
+#pragma unroll
+            for (int p = 0; p < NP; ++p)
+                few |= (fabsf(acc[p][v]) < lim) & (where[1][p0 + p * 32 + (lane & 31)] >= 0);
+        }
+        again = again || __any(few);
+    }
     if (again) h2_again<NP, PRE, XY, SMALL>(h, tile, kb, p0, c_lo, c_hi, lane, acc);
     // Accumulator element 4 j + v of lane (i, g): channel 8 j + 4 g + v of the
     // block, pixel i.  Every operand of the epilogue is loaded before the first
@@ -674,7 +820,7 @@ __global__ __launch_bounds__(64 * kH2Waves, 2) void conv2d_h2(H2Args h) {
         const int q = wk * 32 + 4 * (lane >> 5) + 8 * j;
         bias[j] = *reinterpret_cast<const v4f*>(&lbias[q]);
 #pragma unroll
-        for (int v = 0; v < 4; ++v) ex4[j][v] = again ? 0 : -ex - (PRE ? lexp[q + v] : ew);
+        for (int v = 0; v < 4; ++v) ex4[j][v] = again ? 0 : -ex - h2_channel_exponent(lexp[q + v]);
     }
     const int ohw = a.OH * a.OW;
     const bool relu = a.act == NEO_ACT_RELU;

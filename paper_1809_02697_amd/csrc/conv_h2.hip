@@ -22,20 +22,31 @@ __global__ __launch_bounds__(256) void h2_split_filter(const float* w, int KB, i
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
     __syncthreads();
     m = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-    const int e = h2_exponent(__float_as_uint(m));
-    if (threadIdx.x == 0) wexp[k] = e;
-    const float s = ldexpf(1.f, e), s2 = s * 2048.f;
+    const int e = h2_exponent(__float_as_uint(m), kH2TopAll);
+    const unsigned limit = h2_key(h2_small(e));
+    int small = 0;
+    const float s2 = ldexpf(1.f, e + 11);
     for (long t = threadIdx.x; t < 2L * steps; t += 256) {
         const long f = t >> 1;
         const int g = (int)(t & 1);
         v4h h[2], l[2];
 #pragma unroll
-        for (int q = 0; q < 2; ++q)
-            h2_terms(real ? src[f * 64 + (2 * g + q) * 16] : v4f{0.f, 0.f, 0.f, 0.f}, s, s2, h[q], l[q]);
+        for (int q = 0; q < 2; ++q) {
+            const v4f x = real ? src[f * 64 + (2 * g + q) * 16] : v4f{0.f, 0.f, 0.f, 0.f};
+            h2_terms(x, s2, h[q], l[q]);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) small += h2_key(x[j]) < limit ? 1 : 0;
+        }
         v8h* dst = out + ((long)kb * steps + f) * 128 + g * 32 + i;
         dst[0] = h2_join(h[0], h[1]);
         dst[64] = h2_join(l[0], l[1]);
     }
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) small += __shfl_xor(small, d, 64);
+    __shared__ int count[4];
+    if ((threadIdx.x & 63) == 0) count[threadIdx.x >> 6] = small;
+    __syncthreads();
+    if (threadIdx.x == 0) wexp[k] = h2_channel(e, count[0] + count[1] + count[2] + count[3]);
 }
 
 }  // namespace
