@@ -529,6 +529,8 @@ __global__ __launch_bounds__(64 * kH2Waves, h2_resident(NP, UC * NI, PRE, SMALL)
         unsigned t = 0;
 #pragma unroll
         for (int w = 0; w < kH2Waves; ++w) t = max(t, top[w]);
+        // (a sample of zeros, or with an infinity, says nothing: values about 1)
+        if (t == 0 || t >= 0x7f800000u) t = 0x3f800000u;
         ex = __builtin_amdgcn_readfirstlane(h2_exponent(t, kH2TopSample));
     }
     const float sclx2 = ldexpf(1.f, ex + 11), sclw2 = ldexpf(1.f, ew + 11);
