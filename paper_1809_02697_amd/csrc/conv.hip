@@ -98,10 +98,20 @@ int h2_pixels(const ConvConfig& c) { return 32 * c.fp * (kH2Waves / c.fk); }
 
 }  // namespace
 
+// Short reductions keep the float32 kernel.  A two-term product is off by up to
+// a few units of its last place, a sum of many is closer than the float32
+// kernel's (it is rounded once per 16 products); where one outweighs the other
+// was measured against float64, relative error in 1e-8, two-term and float32
+// (a chain of one wave, as that kernel runs launches that fill the chip):
+// 1 product 6.8 / 2.6, 9 8.4 / 5.3, 16 8.4 / 7.3, 20 8.3 / 8.2, 24 8.5 / 9.0,
+// 32 8.6 / 10, 64 9.2 / 14, 576 17 / 42.  Of one or two channels, whose steps
+// are mostly padding: 25 10.1 / 8.8, 36 10.8 / 10.7, 42 11.1 / 11.4, 49 11.9 / 12.2.
+static bool h2_long_enough(const ConvShape& s) { return s.C * s.R * s.S >= (s.C < 3 ? 42 : 24); }
+
 bool conv_h2_config_valid(const ConvShape& s, const ConvConfig& c) {
     // (the folded global pool needs the tile kernel's epilogue)
     if (!conv_h2(c) || !(c.fk == 2 || c.fk == 4) || !(c.fp == 2 || c.fp == 4) || c.split < 1 || c.split > 64 ||
-        s.gap || (conv_small_c(s) && c.split > 1))
+        s.gap || (conv_small_c(s) && c.split > 1) || !h2_long_enough(s))
         return false;
     H2Geometry g;
     return h2_geometry(s, h2_pixels(c), &g) && g.tiles * cdiv(cdiv(s.K, s.yb) * s.yb, 32 * c.fk) * c.split < (1L << 30) &&

@@ -13,7 +13,10 @@
 // The two sums are kept in float32 accumulators of their own (so l needs no
 // further bits of fp16's range) and joined at the end.  Three 32x32x16 fp16
 // instructions (96 cycles) replace eight 32x32x2 float32 ones (512 cycles),
-// and the sum is rounded once per 16 products instead of once per 2.
+// and the sum is rounded once per 16 products instead of once per 2: against
+// a float64 reference the result is closer than the float32 kernel's from 24
+// products on; shorter reductions keep that kernel (the measured errors stand
+// at h2_long_enough, conv.hip).
 //
 // Range.  Filters are scaled per output channel, inputs per workgroup.  The
 // scale puts the largest magnitude of a converted channel at 2^14 .. 2^15; of
