@@ -7,6 +7,8 @@
 // contiguous, the plain side 64-byte runs of channel planes.  Blocks of 1 or 2
 // channels use an element-wise path.  All paths are pure permutations plus
 // zero fill: bit-exact.
+#include <algorithm>
+
 #include "neo_internal.h"
 
 namespace neo {
@@ -159,6 +161,15 @@ inline dim3 grid_for(long total) {
     return dim3((unsigned)b);
 }
 
+__global__ __launch_bounds__(256) void fill_kernel(float* p, long n) {
+    for (long i = blockIdx.x * 256L + threadIdx.x; i < n; i += gridDim.x * 256L) {
+        // (a multiplicative hash of the index, mixed once)
+        unsigned h = (unsigned)i * 2654435761u;
+        h = (h ^ (h >> 15)) * 2246822519u;
+        p[i] = (float)(int)(h ^ (h >> 13)) * 0x1p-31f;
+    }
+}
+
 }  // namespace
 
 hipError_t launch_layout_transform(const float* src, int sb, float* dst, int db, int N, int C,
@@ -181,6 +192,12 @@ hipError_t launch_layout_transform(const float* src, int sb, float* dst, int db,
         hipLaunchKernelGGL(any_to_any, grid_for((long)N * Cd * H * W), dim3(256), 0, st, src, sb,
                            dst, db, N, C, H, W, c_off, c_tot);
     }
+    return hipGetLastError();
+}
+
+hipError_t launch_fill(float* p, long n, hipStream_t st) {
+    if (n <= 0) return hipSuccess;
+    hipLaunchKernelGGL(fill_kernel, dim3((unsigned)std::min<long>(4096, (n + 255) / 256)), dim3(256), 0, st, p, n);
     return hipGetLastError();
 }
 

@@ -395,6 +395,8 @@ hipError_t launch_layout_transform(const float* src, int sb, float* dst, int db,
                                    int H, int W, int dst_off, int dst_tot, hipStream_t st);
 hipError_t launch_pack_filter(const float* w, int K, int C, int R, int S, int ib, int ob,
                               float* out, hipStream_t st);
+// n floats in [-1, 1), by their index.
+hipError_t launch_fill(float* p, long n, hipStream_t st);
 
 // ---- pools ----------------------------------------------------------------------------
 hipError_t launch_maxpool(const PoolShape& s, const float* x, float* y, hipStream_t st);

@@ -1526,7 +1526,7 @@ std::vector<int> candidate_blocks(int C, int D, bool input_side) {
 // NEO_PLAN_GLOBAL_SEARCH: measure every candidate scheme of every conv without
 // a given scheme (the local search, its best launch configuration and time
 // per (workload, ic_bn, oc_bn)) and every layout transform the program asks
-// about, on zero-filled scratch buffers, then run the program and fix each
+// about, on scratch buffers of ordinary values, then run the program and fix each
 // conv's scheme.
 int search_schemes(neo_plan* P) {
     hipError_t e;
@@ -1554,10 +1554,11 @@ int search_schemes(neo_plan* P) {
     if (e == hipSuccess) e = hipMalloc(&Rz, max_act * 4);
     if (e == hipSuccess) e = hipMalloc(&Wt, max_w * 4);
     if (e == hipSuccess) e = hipMalloc(&Bz, max_b * 4);
+    // (ordinary values: a two-term launch's time depends on them)
     for (auto* b : {X, Y, Rz})
-        if (e == hipSuccess) e = hipMemset(b, 0, max_act * 4);
-    if (e == hipSuccess) e = hipMemset(Wt, 0, max_w * 4);
-    if (e == hipSuccess) e = hipMemset(Bz, 0, max_b * 4);
+        if (e == hipSuccess) e = launch_fill(b, max_act, st);
+    if (e == hipSuccess) e = launch_fill(Wt, max_w, st);
+    if (e == hipSuccess) e = launch_fill(Bz, max_b, st);
     int rc = e == hipSuccess ? NEO_OK : fail(NEO_ERR_OOM, "neo_plan_create: search buffers");
     // the first failed measurement (the program itself only sees an infinite time)
     int merr = NEO_OK;
@@ -2171,13 +2172,15 @@ static int tune_plan(neo_plan* P) {
         e = hipStreamCreateWithFlags(&P->cap_stream, hipStreamNonBlocking);
         if (e != hipSuccess) return hip_fail(e, "neo_plan_create: tuning stream");
     }
-    // stand-in input / output of the network's shapes (contents do not matter)
+    // Stand-in input / output of the network's shapes, and all activations, hold
+    // ordinary values: the time of a two-term launch depends on them (a value out
+    // of the range of its scale has the tile taken again in float32).
     const Val& in = P->vals[P->input_val];
     const Val& out = P->vals[P->out_val];
     float *xin = nullptr, *yout = nullptr;
     e = hipMalloc(&xin, std::max<size_t>((size_t)in.N * in.C * in.H * in.W * 4, 256));
     if (e == hipSuccess) e = hipMalloc(&yout, std::max<size_t>((size_t)out.N * out.C * out.H * out.W * 4, 256));
-    if (e == hipSuccess) e = hipMemset(xin, 0, (size_t)in.N * in.C * in.H * in.W * 4);
+    if (e == hipSuccess) e = launch_fill(xin, (long)in.N * in.C * in.H * in.W, P->cap_stream);
     int rc = e == hipSuccess ? NEO_OK : fail(NEO_ERR_OOM, "neo_plan_create: tuning buffers");
     // a pair stays only where it beats its two convs' own best launches;
     // appends what runs (the pair, or the two convs) and its time
@@ -2215,6 +2218,13 @@ static int tune_plan(neo_plan* P) {
     std::vector<Step> next;
     for (Step& s : P->steps) {
         if (rc != NEO_OK) break;
+        // (again for every step: of the steps before it only the convs ran, each
+        // over its own stand-ins)
+        e = launch_fill(reinterpret_cast<float*>(P->d_act), P->act_bytes / 4, P->cap_stream);
+        if (e != hipSuccess) {
+            rc = hip_fail(e, "neo_plan_create: tuning values");
+            break;
+        }
         if (s.kind == ST_CONV_GROUP && s.i8 && !s.tuned) {
             // integer convs: the group (with its pool), the group with the
             // pool alone, or every conv alone (each in its own output mode)
@@ -2452,6 +2462,9 @@ static int tune_plan(neo_plan* P) {
         }
         next.push_back(s);
     }
+    // (the values of a last step that nothing was timed for)
+    if (rc == NEO_OK && (e = hipStreamSynchronize(P->cap_stream)) != hipSuccess)
+        rc = hip_fail(e, "neo_plan_create: tuning values");
     if (rc == NEO_OK) P->steps.swap(next);
     // groups the search split up: their convs' quantization passes again at
     // each copy's first reader

@@ -324,6 +324,31 @@ def test_infinities_and_nans(neo, cfg, monkeypatch, tmp_path):
             assert spread(v, np.where(np.isfinite(v), ref, np.nan), cond, C * 25, (cfg, kind)) < 2.0 ** -21
 
 
+def test_search_times_ordinary_values(neo):
+    """The local search times its launches over activations of ordinary values
+    (a two-term launch's time depends on them), not over what the allocation
+    held or the launches before it left: a later conv alone, after it, sums
+    inputs of [-1, 1) with weights that keep their scale."""
+    neo.tune_db_clear()
+    rng = np.random.default_rng(5)
+    w = [rng.normal(0, np.sqrt(3.0 / (c * 9)), (64, c, 3, 3)).astype(np.float32) for c in (32, 64)]
+    g = wl.Graph(name="two", input_shape=(2, 32, 24, 24))
+    zero = np.zeros(64, np.float32)
+    g.nodes = [wl.Node(op="input")] + [wl.Node(op="conv", inputs=(i,), K=64, R=3, S=3, pad=(1, 1), w=w[i], bias=zero)
+                                       for i in (0, 1)] + [wl.Node(op="output", inputs=(2,))]
+    p = neo.Plan(g, flags=neo.PLAN_TUNE)
+    steps = p.describe()["steps"]
+    last = max(i for i, s in enumerate(steps) if s["kind"] == "conv")
+    x, out = dev(np.zeros(g.input_shape, np.float32)), dev(np.zeros((2, 64, 24, 24), np.float32))
+    p.run_step(last, x, out)
+    for i in range(last + 1, len(steps)):
+        p.run_step(i, x, out)
+    y = host(out)
+    p.destroy()
+    neo.tune_db_clear()
+    assert 0.3 < y.std() < 3 and np.abs(y).max() < 10
+
+
 def test_refused_where_it_does_not_apply(neo, tmp_path):
     """A window whose patch exceeds the workgroup's, and a reduction of few
     products (whose error would be larger than the float32 kernel's), keep the
