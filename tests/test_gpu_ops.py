@@ -221,6 +221,22 @@ def test_dense(neo, N, IN, OUT, act):
     assert_close(y, ref, "dense")
 
 
+@pytest.mark.parametrize("N,IN,OUT", [
+    (17, 20, 2100),     # 32 images a tile: less than two chunks of the reduction,
+    (19, 100, 2100),    # an odd number of chunks and a part of one, the last images' rows missing,
+    (32, 37, 4099),     # rows that are not 16-byte aligned,
+    (33, 56, 1400),     # two output tiles for 32 images: the same three,
+    (33, 101, 1400),
+    (40, 48, 1500),     # an odd number of whole chunks,
+    (64, 4100, 1500),   # more pairs of chunks than waves
+])
+def test_dense_tiles_for_several_images(neo, N, IN, OUT):
+    """The tiles that launches of more than 256 16 x 16 tiles take: 16 outputs x
+    32 images up to 32 images, 32 x 32 beyond."""
+    assert -(-OUT // 16) * -(-N // 16) > 256
+    test_dense(neo, N, IN, OUT, "relu" if N % 2 else "none")
+
+
 CONFIGS = [(fk, fp, sp, wv) for fk in (1, 2, 4) for fp in (1, 2, 4) for wv in (1, 2, 4, 8, 16)
            for sp in (1, 3) if wv <= 4 or (wv == 8 and fk * fp <= 4) or (wv == 16 and fk * fp <= 2)]
 
