@@ -198,9 +198,10 @@ namespace {
 // share its matrix and vector units, where a step takes 96 fp + 181 cycles and
 // a float4 264.  The constants are a fit to 2,174 measured launches (220
 // shapes of 1x1 to 7x7 kernels at batch 1 to 32, every tile, splits 1 to 8):
-// mean deviation 11 %.  (Fitted before the LDS reads moved into the matrix
-// instructions' shadow, which took up to 9 % off launches that fill the chip and
-// added 3 % to some others; not fitted again.)
+// mean deviation 11 %.  Against the kernel as it is now, over 30,701 launches of
+// 3,357 other shapes: 12 %.  A new fit to those brings it to 9 % and makes the
+// same choices (within 5 % of the best for 90 against 89 % of the shapes), so
+// the constants stay.
 double h2_time_us(const ConvShape& s, const ConvConfig& c) {
     H2Geometry g;
     if (!conv_h2_config_valid(s, c) || !h2_geometry(s, h2_pixels(c), &g)) return 1e30;
@@ -220,10 +221,12 @@ double h2_time_us(const ConvShape& s, const ConvConfig& c) {
     return us;
 }
 
-// The tile kernel's model is too fast by 1.2 to 2.3 (the middle half of those
-// shapes: 1.3 to 1.8), the two-term kernel's is not, so the line between them
-// lies at 1.4 times the tile model's time: of the 220 shapes 55 then take the
-// two-term kernel, 1.57 times as fast on average, one of them 7 % slower.
+// The tile kernel's model is too fast by 1.4 to 2.5 (the middle half of the 3,357
+// shapes: 1.5 to 2.0), the two-term kernel's is not, so the line between them
+// lies at 1.4 times the tile model's time: 1,393 of the shapes then take the
+// two-term kernel, 1.66 times as fast on average, 14 of them more than 5 % slower
+// (the worst 12 %).  At 1.3 that is 1 shape and 0.5 % more time on average, at
+// 1.5 65 shapes and 0.2 % less.
 constexpr double kH2Line = 1.4;
 
 }  // namespace
