@@ -51,6 +51,16 @@ sys.path.insert(0, ROOT)
 
 PEAK_FP32_TFLOPS = 157.3    # MI355X dense fp32 matrix peak
 PEAK_HBM_GBS = 8000.0       # MI355X HBM3E
+# A convolution on two-term fp16 operands takes three fp16 products for one
+# float32 product: a third of the dense fp16 matrix peak (2.5 PFLOP/s).
+PEAK_TWO_TERM_TFLOPS = 2500.0 / 3
+
+
+def conv_peak(cfg):
+    """The matrix peak of a conv launch's number format (waves = 0 names the
+    two-term kernel)."""
+    two_term = cfg.get("algo", "direct") == "direct" and cfg.get("waves") == 0
+    return PEAK_TWO_TERM_TFLOPS if two_term else PEAK_FP32_TFLOPS
 
 
 def conv_costs(C, K, R, S, H, W, st, pd, N=1, residual=False):
@@ -375,7 +385,7 @@ def layer_table(torch, plan, x, out, reps, cold=True, cold_hbm_only=False, selec
         key += (json.dumps(cfg, sort_keys=True),)
         us = time_graph(torch, lambda: plan.run_step(i, x, out), reps)
         f_, b_ = launch_costs(members)
-        hbm = f_ / b_ * PEAK_HBM_GBS / 1e3 < PEAK_FP32_TFLOPS
+        hbm = f_ / b_ * PEAK_HBM_GBS / 1e3 < conv_peak(cfg)
         cold_us = (time_cold(torch, lambda: plan.run_step(i, x, out), max(4, reps // 2))
                    if cold and (hbm or not cold_hbm_only) else 0.0)
         if key in rows:
@@ -395,11 +405,12 @@ def layer_table(torch, plan, x, out, reps, cold=True, cold_hbm_only=False, selec
         tf = r["flops"] / (us * 1e-6) / 1e12
         gbs = r["bytes"] / (us * 1e-6) / 1e9
         ai = r["flops"] / r["bytes"]
-        roof = min(PEAK_FP32_TFLOPS, ai * PEAK_HBM_GBS / 1e3)
+        peak = conv_peak(r["config"])
+        roof = min(peak, ai * PEAK_HBM_GBS / 1e3)
         r.update(us=round(us, 2), gflop=round(r["flops"] / 1e9, 4), tflops=round(tf, 2),
                  alg_gbs=round(gbs, 1),
-                 bound="mfma" if ai * PEAK_HBM_GBS / 1e3 >= PEAK_FP32_TFLOPS else "hbm",
-                 pct_mfma=round(100 * tf / PEAK_FP32_TFLOPS, 1),
+                 bound="mfma" if ai * PEAK_HBM_GBS / 1e3 >= peak else "hbm",
+                 mfma_peak=round(peak, 1), pct_mfma=round(100 * tf / peak, 1),
                  pct_hbm=round(100 * gbs / PEAK_HBM_GBS, 1), pct_roof=round(100 * tf / roof, 1))
         if cold and cold_us > 0:
             r.update(cold_us=round(cold_us, 2),
@@ -764,8 +775,10 @@ def main():
         tot_t = sum(r["us"] * 1e-6 * r["uses"] for r in layers)
         n_launch = sum(r["uses"] for r in layers)
         achieved = tot_f / tot_t / 1e12
-        roofline = dict(bound="mfma", achieved=round(achieved, 2), peak=PEAK_FP32_TFLOPS,
-                        unit="TFLOP/s", frac=round(achieved / PEAK_FP32_TFLOPS, 4),
+        # (the launches' own peaks, weighted by their work)
+        peak = tot_f / sum(r["flops"] * r["uses"] / conv_peak(r["config"]) for r in layers)
+        roofline = dict(bound="mfma", achieved=round(achieved, 2), peak=round(peak, 1),
+                        unit="TFLOP/s", frac=round(achieved / peak, 4),
                         traffic=measured_traffic(),
                         kernel="conv2d_blocked (single, fused-group, pointwise-pair and 3x3-chain "
                                "launches, each with its split-reduction pass)",

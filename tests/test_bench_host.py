@@ -16,6 +16,13 @@ sys.path.insert(0, ROOT)
 import bench  # noqa: E402
 
 
+def test_conv_peak_by_number_format():
+    assert bench.conv_peak({"tile": [4, 4], "waves": 4, "algo": "direct"}) == bench.PEAK_FP32_TFLOPS
+    assert bench.conv_peak({"tile": [4, 0], "waves": 2, "algo": "direct"}) == bench.PEAK_FP32_TFLOPS
+    assert bench.conv_peak({"tile": [2, 2], "waves": 4, "algo": "winograd"}) == bench.PEAK_FP32_TFLOPS
+    assert bench.conv_peak({"tile": [4, 4], "waves": 0, "algo": "direct"}) == bench.PEAK_TWO_TERM_TFLOPS
+
+
 def test_conv_costs_closed_forms():
     # 3x3 s1 p1, 64 -> 64 at 56 x 56: 2 K C R S OH OW flops; input, filter,
     # output and bias once
