@@ -26,6 +26,15 @@
  *     [N][C][H][W].  Filters in KCRS[16]c[16]k are
  *     [ceil(K/16)][ceil(C/16)][R][S][16 (c)][16 (k)], output channel
  *     innermost, zero padded.
+ *   - Direct float32 convolutions hold every output within the a-priori error of a
+ *     float32 sum of its own terms, for operands of any range; infinities and
+ *     NaN reach the outputs whose windows hold them.  Launches that fill the
+ *     chip, of at least 24 products per output, take each operand as two fp16
+ *     terms (22 bits and a sign, scaled per filter channel and per tile of the
+ *     input; the product of both second terms, below 2^-22 of a product, is
+ *     dropped) and sum in float32.  Sums that the terms do not hold, beside
+ *     magnitudes too far apart, are computed again on float32 operands: the
+ *     same result at up to 1.6 times the float32 kernel's time.
  *   - Every device call is asynchronous on `stream` (a hipStream_t; NULL is
  *     the null stream) and never synchronizes.  A kernel fault surfaces at
  *     the caller's next synchronization.

@@ -2218,9 +2218,11 @@ static int tune_plan(neo_plan* P) {
     std::vector<Step> next;
     for (Step& s : P->steps) {
         if (rc != NEO_OK) break;
-        // (again for every step: of the steps before it only the convs ran, each
-        // over its own stand-ins)
-        e = launch_fill(reinterpret_cast<float*>(P->d_act), P->act_bytes / 4, P->cap_stream);
+        // (again for every step that is timed: of the steps before it only the
+        // convs ran, each over its own stand-ins)
+        const bool convs = s.kind == ST_CONV || s.kind == ST_CONV_GROUP || s.kind == ST_CONV_PAIR ||
+                           s.kind == ST_CONV_CHAIN || s.kind == ST_CONV_POOL;
+        if (convs && !s.tuned) e = launch_fill(reinterpret_cast<float*>(P->d_act), P->act_bytes / 4, P->cap_stream);
         if (e != hipSuccess) {
             rc = hip_fail(e, "neo_plan_create: tuning values");
             break;
