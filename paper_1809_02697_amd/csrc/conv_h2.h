@@ -555,6 +555,7 @@ __global__ __launch_bounds__(64 * kH2Waves, h2_resident(NP, UC * NI, PRE, SMALL)
                 reinterpret_cast<v4h*>(&xl[0][c][e][xq >> 1][xp + 64 * j] + at)[xq & 1] = t[e];
         }
     };
+    // (the barrier that follows makes the wave's count so far visible too)
     auto stage = [&](int at) __attribute__((always_inline)) {
         unsigned low = ~0u;
 #pragma unroll
@@ -568,6 +569,7 @@ __global__ __launch_bounds__(64 * kH2Waves, h2_resident(NP, UC * NI, PRE, SMALL)
                 for (int j = 0; j < NI; ++j)
 #pragma unroll
                     for (int e = 0; e < 4; ++e) n_small += __popcll(__ballot(h2_key(xv[c][j][e]) < x_small));
+            small[wave] = n_small;  // (by all lanes)
         }
     };
 
@@ -595,6 +597,7 @@ __global__ __launch_bounds__(64 * kH2Waves, h2_resident(NP, UC * NI, PRE, SMALL)
         lbias[threadIdx.x] = my_bias;
         if constexpr (PRE) lexp[threadIdx.x] = my_exp;
     }
+    small[wave] = 0;  // (read behind the barrier of the last staging)
     if constexpr (!PRE) {
         if (lane < 32) lexp[wk * 32 + lane] = h2_channel(ew, 0);
     }
@@ -616,6 +619,8 @@ __global__ __launch_bounds__(64 * kH2Waves, h2_resident(NP, UC * NI, PRE, SMALL)
         xh[p] = read(at[p], 0);
         xlo[p] = read(at[p], 1);
     }
+    unsigned w_low = 0;  // the wave's channels with small filter values
+    if constexpr (PRE) w_low = (unsigned)__ballot(h2_channel_small(lexp[wk * 32 + (lane & 31)]) != 0);
     // off: the step's input from the lane's first (a chunk of one block walks
     // the kernel entries, a pointwise chunk its blocks); left: steps of the
     // chunk from this one on, at least two in a whole chunk
@@ -759,6 +764,11 @@ __global__ __launch_bounds__(64 * kH2Waves, h2_resident(NP, UC * NI, PRE, SMALL)
         step(wv[d], wv[d + 1]);
     }
 
+    // (every wave's count stands since the barrier behind its last staging)
+    unsigned x_count = 0;
+#pragma unroll
+    for (int w = 0; w < kH2Waves; ++w) x_count += small[w];
+    x_count = __builtin_amdgcn_readfirstlane(x_count);
     // join the sums; a non-finite one means a value out of range
     float bad = 0.f;
 #pragma unroll
@@ -769,14 +779,7 @@ __global__ __launch_bounds__(64 * kH2Waves, h2_resident(NP, UC * NI, PRE, SMALL)
             bad = __builtin_fmaf(acc[p][v], 0.f, bad);
         }
     bool again = __any(bad != bad);
-    if (lane == 0) small[wave] = n_small;
-    __syncthreads();
-    unsigned x_count = 0;
-#pragma unroll
-    for (int w = 0; w < kH2Waves; ++w) x_count += small[w];
-    x_count = __builtin_amdgcn_readfirstlane(x_count);
-    const unsigned w_low = PRE ? (unsigned)__ballot(h2_channel_small(lexp[wk * 32 + (lane & 31)]) != 0)
-                               : (unsigned)(w_seen | (w_seen >> 32));
+    if constexpr (!PRE) w_low = (unsigned)(w_seen | (w_seen >> 32));
     if (x_count | w_low) {
         // m small inputs leave a sum an error of at most m 2^-36 times the
         // largest weight (2^15, 2^16 from a sample), m small weights one of m
