@@ -154,8 +154,10 @@ __device__ inline int h2_exponent(unsigned m, int top) {
 __device__ inline unsigned h2_key(float v) { return (__float_as_uint(v) << 1) - 1u; }
 __device__ inline float h2_small(int n) { return ldexpf(1.f, -12 - n); }
 
-// min(m, the values' keys), two keys an instruction.  Of a pair, a zero beside a
-// negative value may read 0 or 1 below its key: small, as zeros are not.
+// min(m, the values' keys), two keys an instruction.  The carry between the two
+// moves the second by at most one, and a zero beside a negative value reads 0:
+// the minimum lies below a limit wherever a small value does, and at times
+// where none does (who counts them looks at the keys themselves).
 __device__ inline unsigned h2_low(const v4f& x, unsigned m) {
     typedef unsigned v2u __attribute__((ext_vector_type(2)));
 #pragma unroll
@@ -499,21 +501,17 @@ __global__ __launch_bounds__(64 * kH2Waves, h2_resident(NP, UC * NI, PRE, SMALL)
     // ---- scales: the input's exponent, and a float32 filter's of the lane's channel
     int ew = 0, ex;
     {
-        constexpr int kMid = SMALL ? 0 : 1;  // further blocks of the sample
-        v4f mid[kMid + 1], wmid[2] = {v4f{0.f, 0.f, 0.f, 0.f}, v4f{0.f, 0.f, 0.f, 0.f}};
-#pragma unroll
-        for (int q = 0; q < kMid; ++q) {
-            const int cm = c_lo + (c_hi - c_lo) * (q + 1) / (kMid + 1);
-            mid[q] = ld4(xr, xoff[(NI - 1) / 2], __builtin_amdgcn_readfirstlane(XY ? xgroup(a, cm) : cm * dx), 0);
+        v4f mid = v4f{0.f, 0.f, 0.f, 0.f}, wmid[2] = {mid, mid};
+        if constexpr (!SMALL) {
+            // (pixels that any but a short last tile has)
+            const int cm = (c_lo + c_hi) / 2;
+            mid = ld4(xr, xoff[(NI - 1) / 2], __builtin_amdgcn_readfirstlane(XY ? xgroup(a, cm) : cm * dx), 0);
+            if constexpr (!PRE) load_w(wmid, __builtin_amdgcn_readfirstlane((f_lo + f_hi) / 2 * kStep));
         }
-        if constexpr (!SMALL && !PRE) load_w(wmid, __builtin_amdgcn_readfirstlane((f_lo + f_hi) / 2 * kStep));
         load_x(xv, c_lo);
 #pragma unroll
         for (int d = 0; d < kRing; ++d) next_w(wv[d]);
-        float mx = 0.f;
-#pragma unroll
-        for (int q = 0; q < kMid; ++q) mx = h2_max(mid[q], mx);
-        mx = h2_wave_max(max_x(xv, mx));
+        const float mx = h2_wave_max(max_x(xv, h2_max(mid, 0.f)));
         if (lane == 0) top[wave] = __float_as_uint(mx);
         if constexpr (!PRE) {
             float mw = h2_max(wmid[0], h2_max(wmid[1], 0.f));
